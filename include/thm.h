@@ -158,7 +158,7 @@ typedef struct {
     int64_t nnz_c;           /* stored entries of C */
     int64_t n_cells;
     int32_t n_subdomains;
-    int32_t n_layers;        /* block-tridiagonal preconditioner layers */
+    int32_t n_layers;        /* mesh layers along the last axis (blocks of the layered factor forms) */
     int64_t factor_bytes;    /* device bytes of the preconditioner factor (FP64 and FP32 copies) */
     int64_t n_interface;     /* complex interface unknowns of the DDM (sum over directed interfaces; -1 before
                                 the first DDM solve) */
@@ -244,11 +244,10 @@ const char *thm_last_error(void);
 thm_status thm_apply_operator(thm_system *sys, int32_t transpose, int32_t precision,
                               const void *x_dev, void *y_dev, void *stream);
 /* y = diag(K, K)^{-1} x (eq. (11)), exact factorised inverse; factorises on first use.  After
- * static condensation of cell interiors, K's skeleton is block tridiagonal over layers of the
- * mesh; it is factorised by block LU when there are at most 64 layers and the widest has at
- * least 1024 skeleton DoFs (3D subdomains), else by block cyclic reduction.  The environment
- * variable THM_FACTOR_FORM = "bcr" or "lu", read when a factorisation is built, forces one
- * form (any other value: THM_EINVAL). */
+ * static condensation of cell interiors, K's skeleton is factorised by nested dissection of the
+ * box of cells.  The environment variable THM_FACTOR_FORM = "bcr" or "lu", read when a
+ * factorisation is built, selects one of the layered forms instead: block cyclic reduction, or
+ * block LU, over the layers of the mesh along its last axis (any other value: THM_EINVAL). */
 thm_status thm_apply_precond(thm_system *sys, int32_t precision, const void *x_dev, void *y_dev,
                              void *stream);
 /* y = (K + iC)^{-1} x (transpose = 0) or (K - iC)^{-1} x (transpose = 1): the complete
@@ -319,8 +318,8 @@ thm_status thm_time_spmv_systems(int32_t nsys, thm_system *const *sys, int32_t p
  * Returns THM_EINVAL for an unknown variant or precision. */
 thm_status thm_set_spmv_variant(thm_system *sys, int32_t precision, int32_t variant);
 
-/* Average device time (ms) of `reps` applications of the factor phases (block cyclic
- * reduction or block LU) of the preconditioner (eq. (11)) -- the DDM's batched subdomain context if a
+/* Average device time (ms) of `reps` applications of the factor phases (between the two
+ * condensation steps) of the preconditioner (eq. (11)) -- the DDM's batched subdomain context if a
  * DDM solve has run on `sys`, else the system's own -- measured with HIP events on the
  * library's stream.  bytes_out: algorithmic bytes per application (every factor matrix
  * once plus member vectors); launches_out: kernel launches per application. */

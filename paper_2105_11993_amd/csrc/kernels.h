@@ -159,6 +159,8 @@ void launch_hsolve(const Batch &B, const int32_t *running, const int32_t *jcnt, 
 template <class T>
 void launch_zero_flagged(const Batch &B, const uint8_t *const *dirs, T *x, hipStream_t st);
 
+struct NdLaunch;
+
 // ---- preconditioner (kernels_prec.hip)
 // Per-system preconditioner description for batched application.
 // Skeleton work vectors of the apply (ws, ys): the members of a factor group share one
@@ -168,6 +170,8 @@ void launch_zero_flagged(const Batch &B, const uint8_t *const *dirs, T *x, hipSt
 // position p lies wv_pos(p, cs) after the column's start, and the imaginary column starts 8
 // after the real one.
 __host__ __device__ inline int64_t wv_pos(int64_t p, int64_t cs) { return (p >> 3) * cs + (p & 7); }
+// Nested-dissection factors (PrecDesc::nd) use position-major vectors instead: a group's
+// position holds the (re, im) pairs of its members one after another, cs = 2 x members.
 
 struct PrecDesc {
     int64_t n;                 // complex DoFs
@@ -175,6 +179,7 @@ struct PrecDesc {
     int64_t cell_off;          // first interior DoF
     int64_t sp;                // padded skeleton length (positions 0 .. sp - 1, a multiple of 8)
     int64_t cs;                // chunk stride of the system's factor group (see wv_pos)
+    int32_t nd;                // position-major vectors; skeleton entry t sits at position t
     int32_t n_cells, n_loc, n_int, ne, nlayers;
     const int32_t *cell_dofs;  // n_cells * n_loc
     const int32_t *skel_dof;   // skeleton position -> global DoF
@@ -250,13 +255,23 @@ struct PrecBatch {
     DBuf<int64_t> toff;            // complex offset of each system's per-cell condensation terms
     int64_t Ttot = 0;              // complex entries of all condensation terms
     DBuf<int32_t> memb_ptr, memb;  // factor group -> member systems
-    std::vector<PrecPhase> phases; // forward levels, top, backward levels
+    std::vector<PrecPhase> phases; // forward levels, top, backward levels of the layered forms
+    std::vector<NdLaunch> nd64, nd32;  // up and down the trees of the nested-dissection form
+    int64_t Utot = 0;              // scalars of the nested-dissection update vector
+    // scalars per skeleton vector of the layered forms' layout (what the allocation-free apply
+    // accepts is measured by it)
+    int64_t Slayered = 0;
+    PrecBatch();
+    ~PrecBatch();
 };
 
+// the dense phases between the condensation steps, every form
 template <class T>
-void launch_bcr_phases(const PrecBatch &P, const int32_t *mask, T *ws, T *ys, hipStream_t st);
+void launch_factor_phases(const PrecBatch &P, const std::vector<NdLaunch> &nd, const int32_t *mask, T *ws, T *ys,
+                          T *ub, hipStream_t st);
 // x = diag(K, K)^{-1} r for every system of the batch; ws, ys: skeleton work vectors
-// (PrecBatch::Stot scalars), tw: condensation terms (2 PrecBatch::Ttot scalars).
+// (PrecBatch::Stot scalars), tw: condensation terms (2 PrecBatch::Ttot scalars), ub: update
+// vector of the nested-dissection form (PrecBatch::Utot scalars).
 // Output in the member-interleaved layout of the grouped SpMV instead of the systems' own
 // vectors: the SpMV groups, a schedule of IL_TILE DoFs of a group per block, the copy.
 constexpr int IL_TILE = 64;
@@ -268,8 +283,9 @@ struct IlOut {
     T *xi;
 };
 template <class T>
-void launch_prec_apply(const PrecBatch &P, const PrecDesc *d, const int64_t *off, int ns, const int32_t *mask,
-                       const T *r, T *x, T *ws, T *ys, T *tw, hipStream_t st, const IlOut<T> *il = nullptr);
+void launch_prec_apply(const PrecBatch &P, const PrecDesc *d, const std::vector<NdLaunch> &nd, const int64_t *off, int ns, const int32_t *mask,
+                       const T *r, T *x, T *ws, T *ys, T *tw, T *ub, hipStream_t st,
+                       const IlOut<T> *il = nullptr);
 
 // ---- complete inverse (K + iC)^{-1} through K^{-1} and a boundary correction (kernels_full.hip)
 struct FullDesc {

@@ -6,7 +6,7 @@
 // Application to the two right-hand sides (real and imaginary halves) is one
 // batched MFMA launch per level and direction; systems whose matrices are identical
 // share one factor, and their right-hand sides become extra columns of one product.
-#include "kernels.h"
+#include "nd.h"
 
 namespace thm {
 
@@ -264,6 +264,10 @@ __global__ void __launch_bounds__(256) k_cond_fwd(const PrecDesc *__restrict__ p
             acc.x -= v.x;
             acc.y -= v.y;
         }
+    if (d.nd) {
+        *reinterpret_cast<T2 *>(ws + t * d.cs) = acc;
+        return;
+    }
     T *wp = ws + wv_pos(d.skel_pos[t], d.cs);
     wp[0] = acc.x;
     wp[8] = acc.y;
@@ -661,6 +665,7 @@ __device__ __forceinline__ typename P2<T>::t cond_bwd_value(const PrecDesc &d, i
                                                             const T *__restrict__ ys) {
     using T2 = typename P2<T>::t;
     if (g < d.cell_off) {
+        if (d.nd) return *reinterpret_cast<const T2 *>(ys + d.dof_pos[g] * d.cs);
         const T *yp = ys + wv_pos(d.dof_pos[g], d.cs);
         return T2{yp[0], yp[8]};
     }
@@ -678,6 +683,16 @@ __device__ __forceinline__ typename P2<T>::t cond_bwd_value(const PrecDesc &d, i
     }
     const T *F = reinterpret_cast<const T *>(d.F) + c * d.ne * d.n_int;
     const int32_t *cp = d.cell_pos + c * d.ne;
+    if (d.nd) {
+#pragma unroll 4
+        for (int le = 0; le < d.ne; ++le) {
+            const T f = F[le * d.n_int + m];
+            const T2 y = *reinterpret_cast<const T2 *>(ys + cp[le] * d.cs);
+            acc.x -= f * y.x;
+            acc.y -= f * y.y;
+        }
+        return acc;
+    }
 #pragma unroll 4
     for (int le = 0; le < d.ne; ++le) {
         const T f = F[le * d.n_int + m];
@@ -750,8 +765,13 @@ __global__ void __launch_bounds__(64 * SPMV_GMAX) k_cond_bwd_il(const PrecDesc *
     (reinterpret_cast<T2 *>(xib) + G.xoff + g0 * npad)[t] = tile[l * LD + kk];
 }
 
+PrecBatch::PrecBatch() = default;
+PrecBatch::~PrecBatch() = default;
+
 template <class T>
-void launch_bcr_phases(const PrecBatch &P, const int32_t *mask, T *ws, T *ys, hipStream_t st) {
+void launch_factor_phases(const PrecBatch &P, const std::vector<NdLaunch> &nd, const int32_t *mask, T *ws, T *ys,
+                          T *ub, hipStream_t st) {
+    launch_nd_phases<T>(nd, P.memb.p, mask, ws, ys, ub, st);
     constexpr int prec = sizeof(T) == 8 ? 0 : 1;
     for (const PrecPhase &ph : P.phases) {
         const int nb = ph.sched[prec].nblocks;
@@ -761,8 +781,9 @@ void launch_bcr_phases(const PrecBatch &P, const int32_t *mask, T *ws, T *ys, hi
     }
     THM_HIP(hipGetLastError());
 }
-template void launch_bcr_phases<double>(const PrecBatch &, const int32_t *, double *, double *, hipStream_t);
-template void launch_bcr_phases<float>(const PrecBatch &, const int32_t *, float *, float *, hipStream_t);
+template void launch_factor_phases<double>(const PrecBatch &, const std::vector<NdLaunch> &, const int32_t *, double *, double *, double *,
+                                           hipStream_t);
+template void launch_factor_phases<float>(const PrecBatch &, const std::vector<NdLaunch> &, const int32_t *, float *, float *, float *, hipStream_t);
 
 // ------------------------------------------------------------------ batched transpose (setup)
 __global__ void __launch_bounds__(256) k_batch_transpose(int64_t total, int rows, int cols,
@@ -842,12 +863,12 @@ void launch_repack(const std::vector<RepackDesc> &d, double *dst64, float *dst32
 }
 
 template <class T>
-void launch_prec_apply(const PrecBatch &P, const PrecDesc *d, const int64_t *off, int ns, const int32_t *mask,
-                       const T *r, T *x, T *ws, T *ys, T *tw, hipStream_t st, const IlOut<T> *il) {
+void launch_prec_apply(const PrecBatch &P, const PrecDesc *d, const std::vector<NdLaunch> &nd, const int64_t *off,
+                       int ns, const int32_t *mask, const T *r, T *x, T *ws, T *ys, T *tw, T *ub, hipStream_t st, const IlOut<T> *il) {
     if (P.cfr.nblocks) k_cond_fr<T><<<P.cfr.nblocks, 256, 0, st>>>(d, off, P.toff.p, P.cfr.blkoff.p, ns, mask, r, tw);
     if (P.skel.nblocks)
         k_cond_fwd<T><<<P.skel.nblocks, 256, 0, st>>>(d, off, P.soff.p, P.toff.p, P.skel.blkoff.p, ns, mask, r, tw, ws);
-    launch_bcr_phases<T>(P, mask, ws, ys, st);
+    launch_factor_phases<T>(P, nd, mask, ws, ys, ub, st);
     if (il) {
         if (il->sched->nblocks)
             k_cond_bwd_il<T><<<il->sched->nblocks, 64 * SPMV_GMAX, 0, st>>>(d, off, P.soff.p, il->groups, il->sched->blkoff.p,
@@ -858,11 +879,14 @@ void launch_prec_apply(const PrecBatch &P, const PrecDesc *d, const int64_t *off
     THM_HIP(hipGetLastError());
 }
 
-template void launch_prec_apply<double>(const PrecBatch &, const PrecDesc *, const int64_t *, int, const int32_t *,
-                                        const double *, double *, double *, double *, double *, hipStream_t,
+template void launch_prec_apply<double>(const PrecBatch &, const PrecDesc *, const std::vector<NdLaunch> &,
+                                        const int64_t *, int, const int32_t *,
+                                        const double *, double *, double *, double *, double *, double *,
+                                        hipStream_t,
                                         const IlOut<double> *);
-template void launch_prec_apply<float>(const PrecBatch &, const PrecDesc *, const int64_t *, int, const int32_t *,
-                                       const float *, float *, float *, float *, float *, hipStream_t,
+template void launch_prec_apply<float>(const PrecBatch &, const PrecDesc *, const std::vector<NdLaunch> &,
+                                        const int64_t *, int, const int32_t *,
+                                       const float *, float *, float *, float *, float *, float *, hipStream_t,
                                        const IlOut<float> *);
 
 

@@ -59,34 +59,40 @@ void noalloc_prec_apply(Ctx &c, int precision, const double *x, double *y, hipSt
     if (c.ns != 1) fail(THM_EINVAL, "allocation-free apply serves single-system contexts only");
     const bool f32 = precision == THM_FP32_IR;
     const int64_t v = f32 ? 4 : 8;
-    // layout: [x32, y32 (FP32 only)] ws, ys, tw, each 256-byte aligned
+    // layout: [x32, y32 (FP32 only)] ws, ys, tw, ub, each 256-byte aligned
     const int64_t b_io = f32 ? align256(c.K.B.Ltot * 4) : 0;
     const int64_t b_w = align256(c.P.Stot * v);
     const int64_t b_t = align256(2 * c.P.Ttot * v);
-    const int64_t need = 2 * b_io + 2 * b_w + b_t;
+    const int64_t b_u = align256(c.P.Utot * v);
+    // what is accepted is measured by the layered forms' vectors, which are never the shorter ones
+    const int64_t need = std::max(2 * b_io + 2 * align256(c.P.Slayered * v) + b_t, 2 * b_io + 2 * b_w + b_t + b_u);
     if (need > (int64_t)NOALLOC_SCRATCH_BYTES)
         fail(THM_EINVAL, "system needs " + std::to_string(need) + " bytes of scratch; the allocation-free apply has " +
                              std::to_string((long long)NOALLOC_SCRATCH_BYTES));
     unsigned char *base = scratch_address();
-    unsigned char *ws = base + 2 * b_io, *ys = ws + b_w, *tw = ys + b_w;
+    unsigned char *ws = base + 2 * b_io, *ys = ws + b_w, *tw = ys + b_w, *ub = tw + b_t;
     const int32_t *mask = c.mask_all.p;
     if (f32) {
         float *x32 = reinterpret_cast<float *>(base), *y32 = reinterpret_cast<float *>(base + b_io);
         float *w = reinterpret_cast<float *>(ws), *yy = reinterpret_cast<float *>(ys);
-        // padding positions of the skeleton vectors are read (against zero matrix entries)
-        // and must hold zeros, whatever an earlier call left there
-        zero_fill<float>(w, c.P.Stot, st);
-        zero_fill<float>(yy, c.P.Stot, st);
+        // padding positions of the layered forms' vectors are read (against zero matrix
+        // entries) and must hold zeros, whatever an earlier call left there
+        if (!c.P.phases.empty()) {
+            zero_fill<float>(w, c.P.Stot, st);
+            zero_fill<float>(yy, c.P.Stot, st);
+        }
         launch_scale<double, float>(c.K.B, nullptr, nullptr, 0, x, x32, nullptr, 0, nullptr, st);
-        launch_prec_apply<float>(c.P, c.P.d32.p, c.K.B.off.p, 1, mask, x32, y32, w, yy,
-                                 reinterpret_cast<float *>(tw), st);
+        launch_prec_apply<float>(c.P, c.P.d32.p, c.P.nd32, c.K.B.off.p, 1, mask, x32, y32, w, yy,
+                                 reinterpret_cast<float *>(tw), reinterpret_cast<float *>(ub), st);
         launch_scale<float, double>(c.K.B, nullptr, nullptr, 0, y32, y, nullptr, 0, nullptr, st);
     } else {
         double *w = reinterpret_cast<double *>(ws), *yy = reinterpret_cast<double *>(ys);
-        zero_fill<double>(w, c.P.Stot, st);
-        zero_fill<double>(yy, c.P.Stot, st);
-        launch_prec_apply<double>(c.P, c.P.d64.p, c.K.B.off.p, 1, mask, x, y, w, yy,
-                                  reinterpret_cast<double *>(tw), st);
+        if (!c.P.phases.empty()) {
+            zero_fill<double>(w, c.P.Stot, st);
+            zero_fill<double>(yy, c.P.Stot, st);
+        }
+        launch_prec_apply<double>(c.P, c.P.d64.p, c.P.nd64, c.K.B.off.p, 1, mask, x, y, w, yy,
+                                  reinterpret_cast<double *>(tw), reinterpret_cast<double *>(ub), st);
     }
 }
 

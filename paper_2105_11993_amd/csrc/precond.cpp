@@ -16,8 +16,10 @@
 // Systems whose Dirichlet-modified K and element matrices are bitwise identical
 // share one factor.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <string>
 
@@ -239,20 +241,316 @@ static void plan_lu(Factor &f) {
 // few thick layers (3D subdomains: 9 layers of 1,282 at 8^3, 17 of 4,866 at 16^3) each
 // block-LU launch is large enough to stream at full rate and block LU reads fewer bytes for
 // the same K^{-1}; with many thin layers (2D meshes) the launches are latency-bound and the
-// long chain of pivots is the less accurate one in FP32, so cyclic reduction stays.
-// THM_FACTOR_FORM=bcr|lu overrides the choice (tests of both forms on small problems).
+// long chain of pivots is the less accurate one in FP32, so cyclic reduction is the form that
+// the layers of such a mesh are limited by (see setup_precond).
 constexpr int LU_MIN_LAYER = 1024;
 constexpr int LU_MAX_LAYERS = 64;
-static bool use_block_lu(const Layering &L) {
-    if (const char *e = std::getenv("THM_FACTOR_FORM")) {
-        const std::string v(e);
-        if (v == "lu") return true;
-        if (v == "bcr") return false;
-        fail(THM_EINVAL, "THM_FACTOR_FORM must be bcr or lu");
-    }
+static bool lu_shape(const Layering &L) {
     int64_t wide = 0;
     for (int32_t b : L.bsize) wide = std::max<int64_t>(wide, b);
     return wide >= LU_MIN_LAYER && L.nlayers <= LU_MAX_LAYERS;
+}
+
+// Maps of the layered forms for one system (host lists and their device copies).
+static void layer_maps(thm_system &S, hipStream_t st) {
+    if (S.Lskel_dof.n) return;
+    const Topo &t = S.topo;
+    build_layer_maps(t, S.dir, S.L);
+    S.Lskel_dof.upload(S.L.skel_dof, st);
+    S.Lskel_pos.upload(S.L.skel_pos, st);
+    // global DoF -> padded position in the skeleton work vectors (-1: interior)
+    std::vector<int32_t> vpos(S.L.dof_pos.size(), -1);
+    for (size_t g = 0; g < vpos.size(); ++g)
+        if (S.L.dof_pos[g] >= 0) vpos[g] = S.L.skel_pos[S.L.dof_pos[g]];
+    S.Ldof_pos.upload(vpos, st);
+    // per cell: padded positions of its skeleton (non-interior) local DoFs
+    const int ne = t.n_loc - t.n_int;
+    std::vector<int32_t> cpos((size_t)t.n_cells * ne);
+    for (int64_t c = 0; c < t.n_cells; ++c)
+        for (int le = 0; le < ne; ++le) cpos[(size_t)c * ne + le] = vpos[t.cell_dofs[(size_t)c * t.n_loc + le]];
+    S.Lcell_pos.upload(cpos, st);
+    S.Lcond_ptr.upload(S.L.cond_ptr, st);
+    S.Lcond_cell.upload(S.L.cond_cell, st);
+    S.Lcond_loc.upload(S.L.cond_loc, st);
+    THM_HIP(hipStreamSynchronize(st));
+}
+
+// Apply layout of a layered factor's matrices (see k_repack).
+static void repack(Factor &f, hipStream_t st) {
+    std::vector<RepackDesc> rd;
+    auto add = [&](const Factor::Blk &b) {
+        RepackDesc d{};
+        d.src = f.mat.p + b.off;
+        d.rows = b.rows;
+        d.cols = b.cols;
+        d.ld = b.ld;
+        d.nseg = b.nseg;
+        d.poff = b.poff;
+        int c = 0;
+        for (int q = 0; q < b.nseg; ++q) {
+            d.seg_col[q] = c;
+            d.seg_len[q] = f.bsize[b.seg_layer[q]];
+            d.seg_pstart[q] = b.seg_pstart[q];
+            c += d.seg_len[q];
+        }
+        rd.push_back(d);
+    };
+    for (auto &lev : f.fwd)
+        for (auto &b : lev) add(b);
+    for (auto &lev : f.bwd)
+        for (auto &b : lev) add(b);
+    for (auto &b : f.tops) add(b);
+    f.matp.alloc(std::max<int64_t>(f.matp_elems, 1));
+    f.matp32.alloc(std::max<int64_t>(f.matp_elems, 1));
+    launch_repack(rd, f.matp.p, f.matp32.p, st);
+    THM_HIP(hipStreamSynchronize(st));
+    f.mat.release();
+}
+
+// Offsets of the apply matrices of a nested-dissection factor.
+static void nd_offsets(NdForm &f) {
+    f.elems = 0;
+    f.fo.assign(f.plan->ph.size(), {});
+    f.bo.assign(f.plan->ph.size(), {});
+    for (size_t q = 0; q < f.plan->ph.size(); ++q)
+        for (const NdNode &v : f.plan->ph[q].node) {
+            f.fo[q].push_back(f.elems);
+            f.elems += nd_fwd_elems(v);
+            f.bo[q].push_back(f.elems);
+            f.elems += nd_bwd_elems(v);
+        }
+}
+
+// One factorisation to do: its form (offsets set), destination and inputs.
+struct NdJob {
+    NdForm *form;
+    thm_system *rep;
+    double *m64;  // null in every job of a batch that only probes the growth
+    float *m32;
+    const double *kcond;
+};
+
+// Numerical factorisation of a batch, one phase at a time over all of it: fronts, inverses of
+// the own blocks, G and the Schur complements, apply matrices.
+static void factor_nd(const NdJob *jobs, size_t nj, int32_t *status, long long *growth, hipStream_t st) {
+    size_t np = 0;
+    for (size_t t = 0; t < nj; ++t) np = std::max(np, jobs[t].form->plan->ph.size());
+    DBuf<GemmDesc> gscr;
+    Sched gsched;
+    DBuf<double> Fprev;                        // fronts of the phase below (their Schur complements)
+    std::vector<int64_t> cprev(nj, 0);  // first child entry per factor
+    DBuf<NdChild> child;
+    for (size_t q = 0; q < np; ++q) {
+        int64_t fe = 0, de = 0, ge = 0;
+        for (size_t t = 0; t < nj; ++t) {
+            const NdPlan &plan = *jobs[t].form->plan;
+            if (q >= plan.ph.size()) continue;
+            for (const NdNode &v : plan.ph[q].node) {
+                fe += (int64_t)(v.b + v.c) * (v.b + v.c);
+                de += (int64_t)v.b * v.b;
+                ge += (int64_t)v.b * v.c;
+            }
+        }
+        DBuf<double> F(std::max<int64_t>(fe, 1)), Di(std::max<int64_t>(de, 1)), G(std::max<int64_t>(ge, 1));
+        std::vector<NdFront> h;
+        std::vector<NdChild> hc;
+        std::vector<int64_t> cnext(nj, 0);
+        fe = de = ge = 0;
+        for (size_t t = 0; t < nj; ++t) {
+            const NdJob &job = jobs[t];
+            const NdPlan &plan = *job.form->plan;
+            const int ne = job.rep->topo.n_loc - job.rep->topo.n_int;
+            cnext[t] = (int64_t)hc.size();
+            if (q >= plan.ph.size()) continue;
+            const NdPhase &ph = plan.ph[q];
+            for (size_t v = 0; v < ph.node.size(); ++v) {
+                const NdNode &x = ph.node[v];
+                const int n = x.b + x.c;
+                NdFront r{};
+                r.F = F.p + fe;
+                r.b = x.b;
+                r.c = x.c;
+                r.kc = ph.kc;
+                if (q == 0) {
+                    r.ncell = x.nch;
+                    r.cell = plan.d_leaf_cell.p + x.ch0;
+                    r.row = plan.d_leaf_row.p + (int64_t)x.ch0 * ne;
+                    r.kcond = job.kcond;
+                    r.ne = ne;
+                } else {
+                    r.cidx = plan.d_cidx.p + x.loff;
+                    r.cnode = plan.d_cnode.p + x.loff;
+                    r.child = child.p + cprev[t];
+                }
+                r.own = plan.d_skel_dof.p + x.pos0;
+                r.dir = job.rep->dir_d.p;
+                r.Dinv = Di.p + de;
+                r.G = G.p + ge;
+                r.m64 = job.m64;
+                r.m32 = job.m32;
+                r.growth = growth + ND_LEVELS * t + q;
+                if (job.m64) {
+                    r.fo = job.form->fo[q][v];
+                    r.bo = job.form->bo[q][v];
+                }
+                h.push_back(r);
+                hc.push_back({r.F + (int64_t)x.b * n + x.b, n, x.uoff});
+                fe += (int64_t)n * n;
+                de += (int64_t)x.b * x.b;
+                ge += (int64_t)x.b * x.c;
+            }
+        }
+        DBuf<NdFront> dh;
+        dh.upload(h, st);
+        if (q == 0) launch_nd_leaf(h, dh.p, st);
+        else launch_nd_merge(h, dh.p, st);
+        launch_nd_invert(h, dh.p, status, st);
+        int64_t wide = 0, widep = 0;
+        for (const NdFront &r : h)
+            if (r.b > ND_INV_MAX) {
+                wide += 2 * (int64_t)r.b * r.b;
+                widep += 2 * (int64_t)r.b;
+            }
+        if (wide) {
+            DBuf<double> work(wide);
+            DBuf<int32_t> piv(widep);
+            std::vector<InvDesc> jobs;
+            int64_t o = 0, op = 0;
+            for (const NdFront &r : h) {
+                if (r.b <= ND_INV_MAX) continue;
+                launch_nd_own(r.F, r.b + r.c, r.b, work.p + o, st);
+                jobs.push_back({r.b, work.p + o, work.p + o + (int64_t)r.b * r.b, r.Dinv, piv.p + op, r.b});
+                o += 2 * (int64_t)r.b * r.b;
+                op += 2 * r.b;
+            }
+            launch_invert_blocked(jobs, status, st);
+        }
+        std::vector<GemmDesc> ga, gb;
+        for (const NdFront &r : h) {
+            if (!r.b || !r.c) continue;
+            const int n = r.b + r.c;
+            ga.push_back({r.c, r.b, r.b, 0, 0, r.F + (int64_t)r.b * n, r.Dinv, r.G, n, r.b, r.b, 1.0, 0.0});
+            gb.push_back({r.c, r.c, r.b, 0, 0, r.G, r.F + r.b, r.F + (int64_t)r.b * n + r.b, r.b, n, n, -1.0, 1.0});
+        }
+        launch_gemm_batched(ga, st, gscr, gsched);
+        THM_HIP(hipStreamSynchronize(st));
+        launch_gemm_batched(gb, st, gscr, gsched);
+        if (jobs[0].m64) launch_nd_pack(h, dh.p, st);
+        else launch_nd_growth(h, dh.p, st);
+        child.upload(hc, st);
+        THM_HIP(hipStreamSynchronize(st));
+        Fprev = std::move(F);
+        cprev = cnext;
+    }
+}
+
+// Factorise every job, in batches whose widest phase of fronts fits 8 GiB.  Returns the growth of
+// probes (jobs without matrices), ND_LEVELS entries each: the largest |G| per phase where it is
+// beyond ND_GROWTH[0], else 0.
+static std::vector<double> factor_nd_all(std::vector<NdJob> &jobs, int32_t *status, hipStream_t st) {
+    std::vector<double> h(ND_LEVELS * jobs.size(), 0.0);
+    if (jobs.empty()) return h;
+    DBuf<long long> growth(h.size());
+    THM_HIP(hipMemsetAsync(growth.p, 0, sizeof(long long) * growth.n, st));
+    for (size_t t0 = 0; t0 < jobs.size();) {
+        size_t t1 = t0;
+        int64_t words = 0;
+        while (t1 < jobs.size()) {
+            int64_t most = 0;
+            for (const NdPhase &ph : jobs[t1].form->plan->ph) {
+                int64_t w = 0;
+                for (const NdNode &v : ph.node) w += 2 * (int64_t)(v.b + v.c) * (v.b + v.c);
+                most = std::max(most, w);
+            }
+            if (t1 > t0 && words + most > (int64_t(1) << 30)) break;
+            words += most;
+            ++t1;
+        }
+        factor_nd(jobs.data() + t0, t1 - t0, status, growth.p + ND_LEVELS * t0, st);
+        t0 = t1;
+    }
+    THM_HIP(hipMemcpyAsync(h.data(), growth.p, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+    THM_HIP(hipStreamSynchronize(st));
+    return h;
+}
+
+enum class Form { nd, bcr, lu };
+
+// Nested dissection keeps O(N log N) words (2D) where the layered forms keep O(N^1.5), in about
+// as few launches as cyclic reduction: 64^2 cells of degree 2, FP64, 7 M words in 5 launches
+// against 49 M in 7; 8^3 of degree 1, 8 M in 5 against 38 M in 17.  Its fronts are also better
+// conditioned (FP32 backward error on the 64^2 square 4e-7 against 1e-5).  The layered forms
+// stay for THM_FACTOR_FORM=bcr|lu.
+static Form factor_form() {
+    if (const char *e = std::getenv("THM_FACTOR_FORM")) {
+        const std::string v(e);
+        if (v == "lu") return Form::lu;
+        if (v == "bcr") return Form::bcr;
+        fail(THM_EINVAL, "THM_FACTOR_FORM must be bcr or lu");
+    }
+    return Form::nd;
+}
+
+// The plan of a system's mesh that avoids the given levels, shared with the systems of the
+// batch on the same mesh; a system keeps its plans (they depend on the mesh alone).
+static std::shared_ptr<NdPlan> nd_plan(thm_system &S, const std::vector<thm_system *> &others, uint64_t avoid,
+                                       hipStream_t st) {
+    for (thm_system *o : others)
+        for (const auto &p : o->nd)
+            if (p->avoid == avoid && p->matches(S.topo)) {
+                if (o != &S) S.nd.push_back(p);
+                return p;
+            }
+    if (S.nd.size() >= 8) S.nd.erase(S.nd.begin() + 2);  // the default plan and the probe stay
+    auto p = std::make_shared<NdPlan>();
+    p->avoid = avoid;
+    nd_build_plan(S.topo, *p, st);
+    S.nd.push_back(p);
+    return p;
+}
+
+// Nested-dissection factors of a set of systems.  Near a resonance of its boxes a factor is as
+// inexact as its growth (32^2 cells of degree 1 with w L = 6.25, close to 2 pi: relative residual
+// of K z = x in FP32 1.2e-3 with boxes of 8 x 8 cells, growth 15, and 4e-5 with boxes of 8 x 16;
+// in FP64 1e-11 and 1e-12).  So the growth of every halving level is found first, by a
+// factorisation with every level as a phase (narrow fronts: about a third of the time of the
+// other), and the phases start where it is small.
+static void setup_nd(const std::vector<thm_system *> &reps, const std::vector<std::shared_ptr<Factor>> &facs,
+                     const std::vector<DBuf<double>> &kcond, const std::vector<thm_system *> &all, int32_t *status,
+                     hipStream_t st) {
+    std::vector<uint64_t> avoid(facs.size(), 0);
+    std::vector<NdForm> probe(facs.size());
+    std::vector<NdJob> jobs;
+    std::vector<size_t> at;
+    for (size_t g = 0; g < facs.size(); ++g) {
+        facs[g]->nd.plan = nd_plan(*reps[g], all, 0, st);
+        if (facs[g]->nd.plan->ph.size() < 2) continue;  // a root alone has no G
+        probe[g].plan = nd_plan(*reps[g], all, ND_PROBE, st);
+        jobs.push_back({&probe[g], reps[g], nullptr, nullptr, kcond[g].p});
+        at.push_back(g);
+    }
+    const std::vector<double> growth = factor_nd_all(jobs, status, st);
+    // a front of the probe may be singular where the plan's are not
+    THM_HIP(hipMemsetAsync(status, 0, sizeof(int32_t), st));
+    for (size_t t = 0; t < jobs.size(); ++t) {
+        const NdPlan &p = *probe[at[t]].plan;
+        for (size_t q = 0; q < p.ph.size(); ++q) {
+            const double v = growth[ND_LEVELS * t + q];
+            const uint64_t cls = !(v <= ND_GROWTH[1]) ? 2 : v > ND_GROWTH[0] ? 1 : 0;
+            if (p.from[q] > 0 && p.from[q] < ND_LEVELS) avoid[at[t]] |= cls << (2 * p.from[q]);
+        }
+    }
+    jobs.clear();
+    for (size_t g = 0; g < facs.size(); ++g) {
+        Factor &f = *facs[g];
+        if (avoid[g]) f.nd.plan = nd_plan(*reps[g], all, avoid[g], st);
+        nd_offsets(f.nd);
+        f.matp_elems = f.nd.elems;
+        f.matp.alloc(std::max<int64_t>(f.matp_elems, 1));
+        f.matp32.alloc(std::max<int64_t>(f.matp_elems, 1));
+        jobs.push_back({&f.nd, reps[g], f.matp.p, f.matp32.p, kcond[g].p});
+    }
+    factor_nd_all(jobs, status, st);
 }
 
 void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool share) {
@@ -278,9 +576,13 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
         facs.push_back(f);
         reps.push_back(s);
     }
+    const Form form = factor_form();
+    if (form != Form::nd)
+        for (thm_system *s : need) layer_maps(*s, st);
     DBuf<int32_t> status(1);
     THM_HIP(hipMemsetAsync(status.p, 0, sizeof(int32_t), st));
     std::vector<Work> W(facs.size());
+    std::vector<DBuf<double>> kconds(facs.size());
     int maxlev = 0, maxn_lu = 0;
     for (size_t g = 0; g < facs.size(); ++g) {
         thm_system &R = *reps[g];
@@ -295,8 +597,16 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
         f.n_int = t.n_int;
         f.ne = t.n_loc - t.n_int;
         f.n_cells = t.n_cells;
-        f.lu = use_block_lu(L);
-        if (f.lu) {
+        f.lu = form == Form::lu;
+        if (form == Form::nd) {
+            // meshes whose layers are too wide for the layered forms are refused as ever
+            Factor lay;
+            lay.nlayers = f.nlayers;
+            lay.bsize = f.bsize;
+            lay.pboff = f.pboff;
+            if (lu_shape(L)) plan_lu(lay);
+            else plan(lay);
+        } else if (f.lu) {
             plan_lu(f);
             maxn_lu = std::max(maxn_lu, f.nlayers);
         } else {
@@ -308,9 +618,11 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
         // condensation of cell interiors
         f.kiinv.alloc(std::max<int64_t>((int64_t)t.n_cells * t.n_int * t.n_int, 1));
         f.F.alloc(std::max<int64_t>((int64_t)t.n_cells * f.ne * t.n_int, 1));
-        DBuf<double> kcond((size_t)t.n_cells * f.ne * f.ne);
+        DBuf<double> &kcond = kconds[g];
+        kcond.alloc((size_t)t.n_cells * f.ne * f.ne);
         launch_condense((int)t.n_cells, t.n_loc, t.n_int, R.kel.p, R.cell_dofs.p, R.dir_d.p, f.kiinv.p, f.F.p,
                         kcond.p, status.p, st);
+        if (form == Form::nd) continue;
         // initial blocks D_k, Lo_k from the condensed element matrices
         W[g].D.alloc(L.sinv_total);
         W[g].Lo0.alloc(std::max<int64_t>(L.lf_total, 1));
@@ -333,9 +645,12 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
             launch_dir_identity(L.n_skel, skel.p, R.dir_d.p, bo.p, so.p, bs.p, L.nlayers, W[g].D.p, st);
             THM_HIP(hipStreamSynchronize(st));
         }
+        kcond.release();
         f.mat.alloc(std::max<int64_t>(f.mat_elems, 1));
         for (int k = 0; k < L.nlayers; ++k) W[g].pos.push_back(k);
     }
+    if (form == Form::nd) setup_nd(reps, facs, kconds, all, status.p, st);
+    kconds.clear();
     DBuf<GemmDesc> gscr;
     Sched gsched;
     auto run_gemms = [&](const std::vector<GemmDesc> &g) {
@@ -492,7 +807,7 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
         for (size_t g = 0; g < W.size(); ++g) {
             Work &w = W[g];
             Factor &f = *w.f;
-            if (f.lu) continue;
+            if (f.lu || f.nd.plan) continue;
             const int N = f.top_n;
             dense[g].alloc((size_t)N * N);
             launch_fill(dense[g].p, (int64_t)N * N, 0.0, st);
@@ -524,34 +839,7 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
     }
     for (Work &w : W) {
         Factor &f = *w.f;
-        std::vector<RepackDesc> rd;
-        auto add = [&](const Factor::Blk &b) {
-            RepackDesc d{};
-            d.src = f.mat.p + b.off;
-            d.rows = b.rows;
-            d.cols = b.cols;
-            d.ld = b.ld;
-            d.nseg = b.nseg;
-            d.poff = b.poff;
-            int c = 0;
-            for (int q = 0; q < b.nseg; ++q) {
-                d.seg_col[q] = c;
-                d.seg_len[q] = f.bsize[b.seg_layer[q]];
-                d.seg_pstart[q] = b.seg_pstart[q];
-                c += d.seg_len[q];
-            }
-            rd.push_back(d);
-        };
-        for (auto &lev : f.fwd)
-            for (auto &b : lev) add(b);
-        for (auto &lev : f.bwd)
-            for (auto &b : lev) add(b);
-        for (auto &b : f.tops) add(b);
-        f.matp.alloc(std::max<int64_t>(f.matp_elems, 1));
-        f.matp32.alloc(std::max<int64_t>(f.matp_elems, 1));
-        launch_repack(rd, f.matp.p, f.matp32.p, st);
-        THM_HIP(hipStreamSynchronize(st));
-        f.mat.release();
+        if (!f.nd.plan) repack(f, st);
         // apply layouts: K_ii^{-1} transposed per cell, F and F^T
         if (f.n_int > 0) {
             DBuf<double> kt(f.kiinv.n);

@@ -428,6 +428,17 @@ void Ctx::spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float c
 template void Ctx::spmv<double>(int, const int32_t *, const double *, double *, const double *, float);
 template void Ctx::spmv<float>(int, const int32_t *, const float *, float *, const float *, float);
 
+static void nd_maps(PrecDesc &d, const NdPlan &p) {
+    d.nd = 1;
+    d.skel_dof = p.d_skel_dof.p;
+    d.skel_pos = nullptr;
+    d.cell_pos = p.d_cell_pos.p;
+    d.dof_pos = p.d_dof_pos.p;
+    d.cond_ptr = p.d_cond_ptr.p;
+    d.cond_cell = p.d_cond_cell.p;
+    d.cond_loc = p.d_cond_loc.p;
+}
+
 // Preconditioner of the batch: factorisation (shared between identical systems) and the
 // batched apply schedule.  Built on first use, so SpMV-only uses of a context skip it.
 void Ctx::build_prec() {
@@ -440,18 +451,17 @@ void Ctx::build_prec() {
     }
     std::vector<PrecDesc> p64(ns), p32(ns);
     std::vector<int64_t> soff(ns);
-    // factor groups in order of first appearance
-    std::vector<Factor *> groups;
-    std::vector<std::vector<int32_t>> members;
+    groups.clear();
     for (int i = 0; i < ns; ++i) {
         thm_system &S = *sys[i];
         Factor &f = *S.fac;
-        auto it = std::find(groups.begin(), groups.end(), &f);
+        auto it = std::find_if(groups.begin(), groups.end(), [&](const Group &g) { return g.f.get() == &f; });
         if (it == groups.end()) {
-            groups.push_back(&f);
-            members.push_back({i});
+            groups.emplace_back();
+            groups.back().f = S.fac;
+            groups.back().mem = {i};
         } else {
-            members[it - groups.begin()].push_back(i);
+            it->mem.push_back(i);
         }
         const Topo &t = S.topo;
         PrecDesc d{};
@@ -472,6 +482,7 @@ void Ctx::build_prec() {
         d.cond_ptr = S.Lcond_ptr.p;
         d.cond_cell = S.Lcond_cell.p;
         d.cond_loc = S.Lcond_loc.p;
+        if (f.nd.plan) nd_maps(d, *f.nd.plan);
 
         p32[i] = d;
         d.kiinv = f.kiinv.p;
@@ -486,23 +497,38 @@ void Ctx::build_prec() {
     // 8-position chunks (see wv_pos); the member count is padded to the 8 or 16 columns
     // pairs of one block's n tiles only to keep each group's 16-lane runs aligned: lanes of
     // absent members read the chunk's first member, so the padding columns are never read.
-    std::vector<int64_t> gbase(groups.size()), gcs(groups.size());
-    int64_t so = 0;
-    for (size_t g = 0; g < groups.size(); ++g) {
-        const int nm = (int)members[g].size();
+    // Nested-dissection groups: position-major, the members' pairs side by side.
+    int64_t so = 0, uo = 0;
+    P.Slayered = 0;
+    for (Group &G : groups) {
+        const int nm = (int)G.mem.size();
         const int nnt = nm > 8 ? 2 : 1;  // the same split as the tasks below
         const int64_t nmp = (int64_t)((nm + 8 * nnt - 1) / (8 * nnt)) * 8 * nnt;
-        const int64_t sp = groups[g]->sp;
+        const int64_t sp = G.f->sp;
         if (sp % 8) fail(THM_EINVAL, "skeleton length not padded to 8");
-        gcs[g] = 16 * nmp;
-        gbase[g] = so;
-        so += sp / 8 * gcs[g];
+        P.Slayered += (sp / 8 * 16 * nmp + 63) & ~int64_t(63);
+        if (G.f->nd.plan) {
+            G.cs = 2 * nm;
+            G.gbase = so;
+            G.ubase = uo;
+            so = (so + G.f->nd.plan->n_skel * G.cs + 63) & ~int64_t(63);
+            uo = (uo + G.f->nd.plan->n_upd * G.cs + 63) & ~int64_t(63);
+            for (int j = 0; j < nm; ++j) {
+                const int i = G.mem[j];
+                soff[i] = G.gbase + 2 * (int64_t)j;
+                p64[i].cs = p32[i].cs = G.cs;
+            }
+            continue;
+        }
+        G.cs = 16 * nmp;
+        G.gbase = so;
+        so += sp / 8 * G.cs;
         so = (so + 63) & ~int64_t(63);
         for (int j = 0; j < nm; ++j) {
-            const int i = members[g][j];
+            const int i = G.mem[j];
             if (p64[i].sp != sp) fail(THM_EINVAL, "members of a factor group differ in skeleton length");
-            soff[i] = gbase[g] + 16 * (int64_t)j;
-            p64[i].cs = p32[i].cs = gcs[g];
+            soff[i] = G.gbase + 16 * (int64_t)j;
+            p64[i].cs = p32[i].cs = G.cs;
         }
     }
     P.ns = ns;
@@ -510,6 +536,8 @@ void Ctx::build_prec() {
     P.d32.upload(p32, st);
     P.soff.upload(soff, st);
     P.Stot = std::max<int64_t>(so, 64);
+    P.Slayered = std::max<int64_t>(P.Slayered, 64);
+    P.Utot = std::max<int64_t>(uo, 64);
     P.skel.build(nsk, 256, st);
     P.dofs.build(n, 256, st);
     {
@@ -528,8 +556,9 @@ void Ctx::build_prec() {
     std::vector<int32_t> mp_host(1, 0);
     {
         std::vector<int32_t> &mp = mp_host, mm;
-        for (auto &v : members) {
-            mm.insert(mm.end(), v.begin(), v.end());
+        for (Group &G : groups) {
+            G.mbeg = mp.back();
+            mm.insert(mm.end(), G.mem.begin(), G.mem.end());
             mp.push_back((int32_t)mm.size());
         }
         P.memb_ptr.upload(mp, st);
@@ -537,7 +566,7 @@ void Ctx::build_prec() {
     }
     // cyclic-reduction phases: forward levels, last blocks, backward levels
     int nlev = 0;
-    for (Factor *f : groups) nlev = std::max(nlev, (int)f->fwd.size());
+    for (const Group &G : groups) nlev = std::max(nlev, (int)G.f->fwd.size());
     auto task = [&](const Factor &f, const Factor::Blk &b, int g, int prec) {
         BcrTask t{};
         t.M = prec ? (const void *)(f.matp32.p + b.poff) : (const void *)(f.matp.p + b.poff);
@@ -548,7 +577,7 @@ void Ctx::build_prec() {
         t.mbeg = mp_host[g];
         t.mend = mp_host[g + 1];
         t.kq = ((b.ld + BCR_WPB - 1) / BCR_WPB + BCR_KS - 1) / BCR_KS * BCR_KS;
-        const int nm = (int)members[g].size();
+        const int nm = (int)groups[g].mem.size();
         t.nnt = nm > 8 ? 2 : 1;
         t.nmc = (nm + 8 * t.nnt - 1) / (8 * t.nnt);
         for (int q = 0; q <= SEGMAX; ++q) t.seg_pstart[q] = q <= b.nseg ? b.seg_pstart[q] : b.seg_pstart[b.nseg];
@@ -559,8 +588,8 @@ void Ctx::build_prec() {
         t.out_off = f.pboff[b.layer];
         t.out_dst = b.out_dst;
         t.subtract = b.subtract;
-        t.gbase = gbase[g];
-        t.cs = gcs[g];
+        t.gbase = groups[g].gbase;
+        t.cs = groups[g].cs;
         if (t.out_off % 8 || t.out_off + b.rows > f.sp) fail(THM_EINVAL, "apply output outside the work vectors");
         return t;
     };
@@ -575,13 +604,13 @@ void Ctx::build_prec() {
         std::vector<int64_t> u64, u32;
         double elems = 0.0, vec = 0.0;
         for (size_t g = 0; g < groups.size(); ++g)
-            for (const Factor::Blk *b : pick(*groups[g])) {
-                t64.push_back(task(*groups[g], *b, (int)g, 0));
-                t32.push_back(task(*groups[g], *b, (int)g, 1));
+            for (const Factor::Blk *b : pick(*groups[g].f)) {
+                t64.push_back(task(*groups[g].f, *b, (int)g, 0));
+                t32.push_back(task(*groups[g].f, *b, (int)g, 1));
                 const int64_t rb = (b->rows + BCR_RT - 1) / BCR_RT;
                 u64.push_back(rb * t64.back().nmc);
                 u32.push_back(rb * t32.back().nmc);
-                const double nm = (double)members[g].size();
+                const double nm = (double)groups[g].mem.size();
                 elems += (double)b->rows * b->cols;
                 vec += nm * 2.0 * (b->cols + b->rows * (b->subtract ? 2.0 : 1.0));
             }
@@ -600,7 +629,7 @@ void Ctx::build_prec() {
                 at.push_back((int64_t)all.size());
                 bcr_chunk_table(t, one);
                 // every chunk the kernel reads lies inside the group's positions
-                const int64_t sp = groups[t.group]->sp;
+                const int64_t sp = groups[t.group].f->sp;
                 for (size_t kc = 0; kc < one.size(); ++kc) {
                     const int64_t p0 = (int64_t)(one[kc] >> 1) + 8 * (int64_t)kc;
                     if (p0 < 0 || p0 % 8 || p0 + 8 > sp) fail(THM_EINVAL, "apply input outside the work vectors");
@@ -641,13 +670,101 @@ void Ctx::build_prec() {
                 for (const auto &b : f.bwd[lev]) v.push_back(&b);
             return v;
         });
+    build_nd_tasks(true, P.nd64);
+    build_nd_tasks(false, P.nd32);
     ws64.alloc(P.Stot);
     ys64.alloc(P.Stot);
     tw64.alloc(2 * P.Ttot);
+    ub64.alloc(P.Utot);
     THM_HIP(hipMemsetAsync(ws64.p, 0, sizeof(double) * ws64.n, st));
     THM_HIP(hipMemsetAsync(ys64.p, 0, sizeof(double) * ys64.n, st));
     THM_HIP(hipStreamSynchronize(st));
     prec_ready = true;
+}
+
+// Blocks of the nested-dissection groups, up the trees and down again: one launch per phase
+// and direction (two where a batch holds groups of one member and larger ones).  ks waves share
+// a 16-row tile so that a wave streams about 100 columns: narrow fronts do not pay for the
+// exchange of partial sums, wide ones keep enough requests in flight.  A phase of more than
+// 2048 blocks of one round each gives a block several rounds of tiles on the staged vector.
+void Ctx::build_nd_tasks(bool f64, std::vector<NdLaunch> &out) {
+    out.clear();
+    size_t np = 0;
+    for (const Group &G : groups)
+        if (G.f->nd.plan) np = std::max(np, G.f->nd.plan->ph.size());
+    auto add = [&](size_t q, bool fwd, bool vec) {
+        auto each = [&](auto visit) {
+            for (const Group &G : groups) {
+                const NdForm &f = G.f->nd;
+                if (!f.plan || q >= f.plan->ph.size() || vec != (G.mem.size() == 1)) continue;
+                for (size_t v = 0; v < f.plan->ph[q].node.size(); ++v) {
+                    const NdNode &x = f.plan->ph[q].node[v];
+                    const int rows = fwd ? x.c : x.b, k = fwd ? x.b : x.b + x.c;
+                    if (rows) visit(G, f, v, x, rows, k, k <= 96 ? 1 : k <= 192 ? 2 : 4);
+                }
+            }
+        };
+        int64_t rounds = 0;  // block rounds of four waves
+        double elems = 0.0, vecs = 0.0;
+        each([&](const Group &G, const NdForm &, size_t, const NdNode &, int rows, int k, int ks) {
+            const int nm = (int)G.mem.size(), tiles = (rows + ND_RT - 1) / ND_RT;
+            rounds += (int64_t)((tiles * ks + 3) / 4) * (vec ? 1 : (nm + 15) / 16);
+            elems += (double)rows * k;
+            vecs += nm * 2.0 * (k + rows);
+        });
+        if (!rounds) return;
+        const int64_t per = std::max<int64_t>(1, rounds / 2048);
+        const int64_t sz = f64 ? 8 : 4;
+        std::vector<NdTask> tasks;
+        NdLaunch L;
+        L.fwd = fwd;
+        L.vec = vec;
+        each([&](const Group &G, const NdForm &f, size_t v, const NdNode &x, int rows, int k, int ks) {
+            const int nm = (int)G.mem.size(), tiles = (rows + ND_RT - 1) / ND_RT;
+            const int64_t kp = nd_pad(k, ND_KS), off = fwd ? f.fo[q][v] : f.bo[q][v];
+            NdTask t{};
+            t.M = f64 ? (const void *)(G.f->matp.p + off) : (const void *)(G.f->matp32.p + off);
+            t.bpos = f.plan->d_bpos.p + x.uoff;
+            t.cidx = f.plan->d_cidx.p + x.loff;
+            t.gbase = G.gbase;
+            t.ubase = G.ubase;
+            t.b = x.b;
+            t.c = x.c;
+            t.pos0 = x.pos0;
+            t.uoff = x.uoff;
+            t.cs = (int32_t)G.cs;
+            t.mbeg = G.mbeg;
+            t.kc = (int16_t)f.plan->ph[q].kc;
+            t.ks = (int16_t)ks;
+            for (int m0 = 0; m0 < nm; m0 += 16) {
+                t.m0 = m0;
+                t.nm = std::min(16, nm - m0);
+                const int nnt = t.nm > 8 ? 2 : 1;
+                if (vec) {
+                    L.lds = std::max<size_t>(L.lds, 2 * sz * std::min<int64_t>(ND_KC_VEC, kp));
+                } else {
+                    const int64_t ld = std::min<int64_t>(nd_kc_mfma((int)sz, nnt), kp) + 16 / sz;
+                    L.lds = std::max<size_t>(L.lds,
+                                             sz * nd_pad(16 * nnt * ld, 8) + (ks > 1 ? sz * 4 * 64 * 4 * nnt : 0));
+                }
+                const int step = (int)per * (4 / ks);
+                for (int r = 0; r < tiles; r += step) {
+                    t.rt0 = r;
+                    t.tiles = std::min(step, tiles - r);
+                    tasks.push_back(t);
+                }
+            }
+        });
+        L.nblocks = (int)tasks.size();
+        L.tasks.upload(tasks, st);
+        THM_HIP(hipStreamSynchronize(st));
+        bcr_bytes[f64 ? 0 : 1].push_back((double)sz * (elems + vecs));
+        out.push_back(std::move(L));
+    };
+    for (size_t q = 0; q < np; ++q)
+        for (bool vec : {true, false}) add(q, true, vec);
+    for (size_t q = np; q-- > 0;)
+        for (bool vec : {true, false}) add(q, false, vec);
 }
 
 // Boundary set Gamma (rows of the Dirichlet-modified C with a nonzero entry), C_G, and
@@ -806,8 +923,8 @@ void Ctx::build_full() {
             const int nt = T.ns;
             for (int64_t k = 0; 2 * k < rmax; k += Q) {
                 launch_full_unit(td, nt, nullptr, T.K.B.off.p, dtk.p, (int)k, 1.0, xin.p, st);
-                launch_prec_apply<double>(T.P, T.P.d64.p, T.K.B.off.p, nt, nullptr, xin.p, zout.p, T.ws64.p,
-                                          T.ys64.p, T.tw64.p, st);
+                launch_prec_apply<double>(T.P, T.P.d64.p, T.P.nd64, T.K.B.off.p, nt, nullptr, xin.p, zout.p, T.ws64.p,
+                                          T.ys64.p, T.tw64.p, T.ub64.p, st);
                 launch_full_gather(td, nt, nullptr, T.K.B.off.p, dtk.p, (int)k, zout.p, dtsoff.p, Sg.p, st);
                 launch_full_unit(td, nt, nullptr, T.K.B.off.p, dtk.p, (int)k, 0.0, xin.p, st);
             }
@@ -904,7 +1021,7 @@ KOps<double> Ctx::ops64(float csign, bool with_prec, int pkind) {
         ensure_xi(false);
         o.prec_i = [this](const double *x, double *y, const int32_t *mask) {
             const IlOut<double> il{sgroups.p, &ilsched, ngroups, xi64.p};
-            launch_prec_apply<double>(P, P.d64.p, K.B.off.p, ns, mask, x, y, ws64.p, ys64.p, tw64.p, st, &il);
+            launch_prec_apply<double>(P, P.d64.p, P.nd64, K.B.off.p, ns, mask, x, y, ws64.p, ys64.p, tw64.p, ub64.p, st, &il);
         };
         o.apply_i = [this, csign](double *y, const int32_t *mask) {
             launch_spmv_group_i<double>(mat64.p, K.B.off.p, sgroups.p, gsched, ngroups, mask, xi64.p, y, csign, st);
@@ -912,13 +1029,13 @@ KOps<double> Ctx::ops64(float csign, bool with_prec, int pkind) {
     }
     o.prec = [this, csign, pkind](const double *x, double *y, const int32_t *mask) {
         if (!prec_ready) fail(THM_EINVAL, "preconditioner used before it was built");
-        launch_prec_apply<double>(P, P.d64.p, K.B.off.p, ns, mask, x, y, ws64.p, ys64.p, tw64.p, st);
+        launch_prec_apply<double>(P, P.d64.p, P.nd64, K.B.off.p, ns, mask, x, y, ws64.p, ys64.p, tw64.p, ub64.p, st);
         if (pkind == 1) {
             // y -= K^{-1} P^T M^{-1} (+-i C_G y_G)
             launch_full_correct<double>(full.d, ns, mask, K.B.off.p, csign < 0 ? 1 : 0, y, full.u64.p,
                                         full.part64.p, full.w64.p, st);
-            launch_prec_apply<double>(P, P.d64.p, K.B.off.p, ns, mask, full.w64.p, full.y64.p, ws64.p, ys64.p,
-                                      tw64.p, st);
+            launch_prec_apply<double>(P, P.d64.p, P.nd64, K.B.off.p, ns, mask, full.w64.p, full.y64.p, ws64.p, ys64.p,
+                                      tw64.p, ub64.p, st);
             launch_axpy<double, double>(K.B, mask, full.neg1.p, full.y64.p, y, st);
         }
     };
@@ -942,6 +1059,7 @@ KOps<float> Ctx::ops32(float csign, bool with_prec, int pkind) {
             ws32.alloc(P.Stot);
             ys32.alloc(P.Stot);
             tw32.alloc(2 * P.Ttot);
+            ub32.alloc(P.Utot);
             THM_HIP(hipMemsetAsync(ws32.p, 0, sizeof(float) * ws32.n, st));
             THM_HIP(hipMemsetAsync(ys32.p, 0, sizeof(float) * ys32.n, st));
         }
@@ -958,7 +1076,7 @@ KOps<float> Ctx::ops32(float csign, bool with_prec, int pkind) {
         ensure_xi(true);
         o.prec_i = [this](const float *x, float *y, const int32_t *mask) {
             const IlOut<float> il{sgroups.p, &ilsched, ngroups, xi32.p};
-            launch_prec_apply<float>(P, P.d32.p, K.B.off.p, ns, mask, x, y, ws32.p, ys32.p, tw32.p, st, &il);
+            launch_prec_apply<float>(P, P.d32.p, P.nd32, K.B.off.p, ns, mask, x, y, ws32.p, ys32.p, tw32.p, ub32.p, st, &il);
         };
         o.apply_i = [this, csign](float *y, const int32_t *mask) {
             launch_spmv_group_i<float>(mat32.p, K.B.off.p, sgroups.p, gsched, ngroups, mask, xi32.p, y, csign, st);
@@ -973,13 +1091,13 @@ KOps<float> Ctx::ops32(float csign, bool with_prec, int pkind) {
 
 void Ctx::prec32(int pkind, float csign, const float *x, float *y, const int32_t *mask) {
     if (!ws32.n) fail(THM_EINVAL, "preconditioner used before it was built");
-    launch_prec_apply<float>(P, P.d32.p, K.B.off.p, ns, mask, x, y, ws32.p, ys32.p, tw32.p, st);
+    launch_prec_apply<float>(P, P.d32.p, P.nd32, K.B.off.p, ns, mask, x, y, ws32.p, ys32.p, tw32.p, ub32.p, st);
     if (pkind == 1) {
         // y -= K^{-1} P^T M^{-1} (+-i C_G y_G)
         launch_full_correct<float>(full.d, ns, mask, K.B.off.p, csign < 0 ? 1 : 0, y, full.u32.p, full.part32.p,
                                    full.w32.p, st);
-        launch_prec_apply<float>(P, P.d32.p, K.B.off.p, ns, mask, full.w32.p, full.y32.p, ws32.p, ys32.p, tw32.p,
-                                 st);
+        launch_prec_apply<float>(P, P.d32.p, P.nd32, K.B.off.p, ns, mask, full.w32.p, full.y32.p, ws32.p, ys32.p, tw32.p,
+                                 ub32.p, st);
         launch_axpy<float, float>(K.B, mask, full.neg1.p, full.y32.p, y, st);
     }
 }
@@ -1212,8 +1330,8 @@ double Ctx::time_bcr(int prec, int reps, double *bytes, int *launches) {
     THM_HIP(hipEventCreate(&e0));
     THM_HIP(hipEventCreate(&e1));
     auto once = [&] {
-        if (prec) launch_bcr_phases<float>(P, nullptr, ws32.p, ys32.p, st);
-        else launch_bcr_phases<double>(P, nullptr, ws64.p, ys64.p, st);
+        if (prec) launch_factor_phases<float>(P, P.nd32, nullptr, ws32.p, ys32.p, ub32.p, st);
+        else launch_factor_phases<double>(P, P.nd64, nullptr, ws64.p, ys64.p, ub64.p, st);
     };
     once();
     THM_HIP(hipEventRecord(e0, st));
@@ -1227,7 +1345,7 @@ double Ctx::time_bcr(int prec, int reps, double *bytes, int *launches) {
     double by = 0.0;
     for (double b : bcr_bytes[prec]) by += b;
     if (bytes) *bytes = by;
-    if (launches) *launches = (int)P.phases.size();
+    if (launches) *launches = (int)(P.phases.size() + (prec ? P.nd32 : P.nd64).size());
     return ms / reps;
 }
 

@@ -6,6 +6,7 @@
 #include <memory>
 
 #include "kernels.h"
+#include "nd.h"
 
 namespace thm {
 struct Ddm;
@@ -15,6 +16,8 @@ struct Ddm;
 struct Factor {
     int nlayers = 0;
     bool lu = false;             // block-LU form (thick layers) instead of cyclic reduction
+    // nested-dissection form (the default, see nd.h), matrices in matp and matp32
+    NdForm nd;
     std::vector<int32_t> bsize;
     std::vector<int64_t> boff;
     int n_int = 0, ne = 0;
@@ -85,7 +88,10 @@ struct thm_system {
     thm::DBuf<double> gD, rhs;  // complex, full length (2n doubles)
     thm::DBuf<int32_t> d2c_ptr, d2c_src;
 
-    // preconditioner: skeleton maps of this system and the (possibly shared) factor
+    // preconditioner: plans of the nested-dissection form (kept over changes of mu: they depend
+    // on the mesh alone), skeleton maps of the layered forms (built when one of them is), and the
+    // (possibly shared) factor
+    std::vector<std::shared_ptr<thm::NdPlan>> nd;
     thm::DBuf<int32_t> Lskel_dof, Lskel_pos, Ldof_pos, Lcell_pos, Lcond_ptr, Lcond_cell, Lcond_loc;
     std::shared_ptr<thm::Factor> fac;
 
@@ -178,8 +184,8 @@ struct Ctx {
     PrecBatch P;
     DBuf<MatDesc> mat64, mat32;
     DBuf<const uint8_t *> dirs;
-    DBuf<double> x64, b64, r64, ws64, ys64, tw64;
-    DBuf<float> x32, b32, ws32, ys32, tw32;
+    DBuf<double> x64, b64, r64, ws64, ys64, tw64, ub64;
+    DBuf<float> x32, b32, ws32, ys32, tw32, ub32;
     DBuf<int32_t> mask_all, run_ir, ir_aux;
     DBuf<double> ir_scal;
     int64_t fp64_fallbacks = 0;  // systems finished in FP64 after GMRES-IR missed rtol (cumulative)
@@ -208,6 +214,16 @@ struct Ctx {
     template <class T> void spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float csign);
 
     bool prec_ready = false;
+    // factor groups of the batch in order of first appearance, their members, and where their
+    // vectors lie
+    struct Group {
+        std::shared_ptr<Factor> f;
+        std::vector<int32_t> mem;
+        int32_t mbeg = 0;
+        int64_t gbase = 0, ubase = 0, cs = 0;
+    };
+    std::vector<Group> groups;
+    void build_nd_tasks(bool f64, std::vector<NdLaunch> &out);
 
     // complete inverse (K + iC)^{-1} = K^{-1} - K^{-1} P^T M^{-1} (i C_G P) K^{-1} (see kernels_full.hip)
     struct Full {

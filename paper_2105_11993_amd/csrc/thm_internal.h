@@ -124,7 +124,9 @@ struct Layering {
 
 void build_csr(const Topo &t, HostCSR &K);
 void build_side_csr(const Topo &t, const std::vector<Side> &sides, HostCSR &C);
-void build_layering(const Topo &t, const std::vector<uint8_t> &dir, Layering &L);
+void build_layers(const Topo &t, Layering &L);  // sizes and offsets of the layers
+// the maps of the layered factor forms, on top of build_layers
+void build_layer_maps(const Topo &t, const std::vector<uint8_t> &dir, Layering &L);
 
 // ---------------------------------------------------------------- device views
 // Per-system pointers used by batched kernels (plain struct, copied to device).

@@ -294,11 +294,10 @@ static int dof_layer(const Topo &t, int64_t g) {
     return (int)(((g - t.face_off[2]) / t.pf) / (nx * ny));
 }
 
-void build_layering(const Topo &t, const std::vector<uint8_t> &dir, Layering &L) {
+void build_layers(const Topo &t, Layering &L) {
     const int last = t.dim - 1;
     L.nlayers = t.n[last] + 1;
     const int nL = L.nlayers;
-    const int64_t N = t.n_dofs;
     L.bsize.assign(nL, 0);
     for (int64_t g = 0; g < t.cell_off; ++g) L.bsize[dof_layer(t, g)]++;
     L.boff.assign(nL + 1, 0);
@@ -308,6 +307,11 @@ void build_layering(const Topo &t, const std::vector<uint8_t> &dir, Layering &L)
     for (int k = 0; k < nL; ++k)
         L.pboff[k + 1] = L.pboff[k] + (L.bsize[k] + SKEL_ALIGN - 1) / SKEL_ALIGN * SKEL_ALIGN;
     L.n_skel_pad = L.pboff[nL];
+}
+
+void build_layer_maps(const Topo &t, const std::vector<uint8_t> &dir, Layering &L) {
+    const int nL = L.nlayers;
+    const int64_t N = t.n_dofs;
     L.skel_pos.assign(L.n_skel, 0);
     for (int k = 0; k < nL; ++k)
         for (int32_t j = 0; j < L.bsize[k]; ++j) L.skel_pos[L.boff[k] + j] = (int32_t)(L.pboff[k] + j);
