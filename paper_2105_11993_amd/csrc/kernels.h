@@ -1,13 +1,19 @@
 // Device descriptors and kernel launchers shared by the HIP sources.
 #pragma once
+#include <algorithm>
 #include <map>
 
 #include "thm_internal.h"
 
 namespace thm {
 
-constexpr int VCHUNK = 4096;  // scalars per block in Krylov vector kernels (even)
-constexpr int NPW = 4;        // partial-sum slots per block (one per wave)
+constexpr int VCHUNK = 1024;  // scalars per block in Krylov vector kernels (a multiple of 1024)
+constexpr int DCHUNK = 2048;  // scalars per block of the inner products, at least
+// Inner-product blocks per column group over the whole batch, about: with fewer, part of the chip
+// idles (128^2 degree 1 in FP64, 22 blocks: 23 us a step, 103: 16), with more, the blocks are
+// mostly prologue and reduction (16 subdomains of 32^2 degree 2 in FP32, 578 blocks: 27 us, 144: 20)
+constexpr int DBLOCKS = 128;
+constexpr int DCOLS = 8;      // basis columns per block of the inner products
 
 struct MatDesc {
     int64_t n;
@@ -78,6 +84,9 @@ struct Batch {
     int64_t Ltot = 0;                  // scalars per vector slot
     Sched vs;                          // VCHUNK scalars per block
     Sched es;                          // 256 complex entries per block
+    DBuf<int32_t> dch;                 // scalars per inner-product block of each system
+    Sched ds;                          // the inner-product blocks
+    int maxd = 0;                      // most inner-product blocks of a system
     std::map<int, Sched> spmv;         // per SpMV variant (10 * lanes_per_row + unroll): 256 / lpr rows per block
     void init(const std::vector<int64_t> &n, int maxcols_, hipStream_t st) {
         ns = (int)n.size();
@@ -97,6 +106,16 @@ struct Batch {
         len.upload(h_len, st);
         nvec.upload(h_nvec, st);
         vs.build(h_len, VCHUNK, st);
+        std::vector<int32_t> c(ns);
+        std::vector<int64_t> nd(ns);
+        for (int s = 0; s < ns; ++s) {
+            c[s] = (int32_t)std::max<int64_t>(DCHUNK, ((Ltot + DBLOCKS - 1) / DBLOCKS + 511) / 512 * 512);
+            nd[s] = (h_len[s] + c[s] - 1) / c[s];
+            maxd = std::max(maxd, (int)nd[s]);
+        }
+        dch.upload(c, st);
+        ds.build(nd, 1, st);
+        THM_HIP(hipStreamSynchronize(st));
         es.build(h_nvec, 256, st);
     }
     const Sched &spmv_sched(int lpr, hipStream_t st) {
@@ -123,17 +142,20 @@ void launch_spmv_group(const MatDesc *mats, const int64_t *off, const SpmvGroup 
 template <class T>
 void launch_spmv_group_i(const MatDesc *mats, const int64_t *off, const SpmvGroup *groups, const Sched &sc, int ng,
                          const int32_t *mask, const T *xi, T *y, float csign, hipStream_t st);
+// step_ctr (may be null) advances by one
 template <class T>
 void launch_dots(const Batch &B, const int32_t *mask, const int32_t *jcnt, const T *V, int64_t ld, const T *w,
-                 double *part, int cplx, hipStream_t st);
+                 double *part, int cplx, int32_t *step_ctr, hipStream_t st);
+// fused: h is formed from the partials of launch_dots (and left in h), else read
 template <class T>
 void launch_cgs_update(const Batch &B, const int32_t *mask, const int32_t *jcnt, const T *V, int64_t ld, T *w,
-                       const double *h, int ldh, double *part, hipStream_t st);
+                       double *h, int ldh, bool fused, const double *part, double *npart, int32_t *jcol,
+                       int32_t *actc, hipStream_t st);
 template <class T>
 void launch_norm2(const Batch &B, const int32_t *mask, const T *x, double *part, hipStream_t st);
 template <class TI, class TO>
 void launch_scale(const Batch &B, const int32_t *mask, const double *scal, int invert, const TI *x, TO *y1,
-                  const int32_t *jcol, int64_t ld1, TO *y2, hipStream_t st, int32_t *step_ctr = nullptr);
+                  const int32_t *jcol, int64_t ld1, TO *y2, hipStream_t st);
 template <class T>
 void launch_lincomb(const Batch &B, const int32_t *mask, const int32_t *kcnt, const T *V, int64_t ld,
                     const double *coef, int ldc, T *y, hipStream_t st);
@@ -141,19 +163,21 @@ template <class TX, class TZ>
 void launch_axpy(const Batch &B, const int32_t *mask, const double *scal, const TZ *z, TX *x, hipStream_t st);
 void launch_norm_finish(const Batch &B, const double *part, const int32_t *mask, double *out, const double *bnorm,
                         double rtol, double *resid, int32_t *running, hipStream_t st);
-void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt, int ncols_fixed,
-                        const double *part, double *out, int ldo, int accumulate, hipStream_t st);
+void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt, const double *part, double *out,
+                        int ldo, int accumulate, hipStream_t st);
 // Start of a cycle: tolerance read from rtol_d; resets *step_ctr (if non-null); writes each
 // system's running flag to hrun (host-visible, may be null).
 void launch_cycle_start(const Batch &B, const double *part, int32_t *running, int32_t *active, int32_t *jcnt,
                         const double *bnorm, const double *rtol_d, double *g, int m, double *beta, double *resid,
                         int32_t *iters, int max_iter, int32_t *step_ctr, int32_t *hrun, hipStream_t st);
-// End of an Arnoldi step: the flags go to host slot (step / spc) mod nslots.
-void launch_arnoldi_finish(const Batch &B, const double *part, int32_t *active, int32_t *jcnt, const double *hcol,
-                           int ldh, double *H, double *cs, double *sn, double *g, double *hnext,
-                           const double *bnorm, const double *rtol_d, int m, int32_t *iters, int max_iter,
-                           double *est, int32_t *hflags, const int32_t *step_ctr, int spc, int nslots,
-                           hipStream_t st);
+// End of an Arnoldi step: V_{j+1} = cur = w / ||w||, column of H; the flags go to host slot
+// (step / spc) mod nslots.
+template <class T>
+void launch_arnoldi_close(const Batch &B, const double *npart, const int32_t *jcol, const int32_t *actc, const T *w,
+                          T *V, int64_t ld, T *cur, const double *hcol, int ldh, double *H, double *cs, double *sn,
+                          double *g, int32_t *active, int32_t *jcnt, double *hnext, const double *bnorm,
+                          const double *rtol_d, int m, int32_t *iters, int max_iter, double *est, int32_t *hflags,
+                          const int32_t *step_ctr, int spc, int nslots, hipStream_t st);
 void launch_hsolve(const Batch &B, const int32_t *running, const int32_t *jcnt, const double *H, const double *g,
                    double *y, int m, hipStream_t st);
 template <class T>

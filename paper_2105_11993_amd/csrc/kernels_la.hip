@@ -407,158 +407,268 @@ template void launch_spmv_group<float>(const MatDesc *, const int64_t *, const S
 // vectors); with cplx = 0 it is the real GMRES of the 2N real block system (the
 // imaginary part of every inner product is dropped).  Hessenberg, Givens and the
 // least-squares solve are FP64 (complex storage in both modes).
-// Each block owns VCHUNK scalars of one system and writes one partial per wave.
+// Elementwise kernels: a block owns VCHUNK scalars of one system; sums leave one partial per
+// block.  The inner products of an Arnoldi step have their own split: a block owns dch[s] scalars
+// (see DBLOCKS) and DCOLS basis columns.
 constexpr int PPT = VCHUNK / 512;  // complex pairs per thread
-constexpr int CG = 4;              // basis columns loaded together
+constexpr int CG = 4;              // basis columns loaded together (lincomb)
+constexpr int UG = 8;              // basis columns loaded together (Gram-Schmidt update)
 
 // Loads stay unconditional (so the compiler keeps them all in flight): lanes past the
 // end of a vector read its last element and their contribution is dropped.
 __device__ __forceinline__ int64_t clampi(int64_t i, int64_t np) { return i < np ? i : np - 1; }
 
-template <class T>
-__device__ __forceinline__ void wave_store(double v, double *dst) {
+// Sum of a block's 256 values, left in thread 0's slot of the partials.
+__device__ __forceinline__ void block_store(double v, double *dst) {
+    __shared__ double lds[4];
     v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) *dst = v;
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) *dst = (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
+// Sum of the partials [b0, b1), the same value in all 256 threads of every block that asks.
+__device__ __forceinline__ double sum_partials(const double *part, int b0, int b1) {
+    __shared__ double lds[4];
+    double a = 0.0;
+    for (int b = b0 + (int)threadIdx.x; b < b1; b += 256) a += part[b];
+    a = wave_sum(a);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = a;
+    __syncthreads();
+    const double r = (lds[0] + lds[1]) + (lds[2] + lds[3]);
+    __syncthreads();
+    return r;
+}
+
+// 16 bytes of a vector: one complex pair in FP64, two in FP32.
+template <class T> struct Pack;
+template <> struct Pack<double> {
+    static constexpr int N = 1;
+    typedef double vec __attribute__((ext_vector_type(2)));
+};
+template <> struct Pack<float> {
+    static constexpr int N = 2;
+    typedef float vec __attribute__((ext_vector_type(4)));
+};
+
+// Inner products of w with DCOLS basis columns over a block's part of a system.  Blocks per
+// system and column group: a single block per chunk (all columns in turn) left most of the chip
+// idle on small and middle-sized systems (128^2 degree 1, 25 columns on average, FP64: 24 us; as
+// split here 16 us).  Slots hold a multiple of 64 scalars, so a 16-byte load never leaves them.
 template <class T>
 __global__ void __launch_bounds__(256) k_dots(const int64_t *__restrict__ off, const int64_t *__restrict__ len,
-                                              const int32_t *__restrict__ blkoff, int ns,
-                                              const int32_t *__restrict__ mask, const int32_t *__restrict__ jcnt,
-                                              const T *__restrict__ V, int64_t ld, const T *__restrict__ w,
-                                              double *__restrict__ part, int maxcols, int cplx) {
-    using T2 = typename V2<T>::t;
+                                              const int32_t *__restrict__ dch, const int32_t *__restrict__ blkoff,
+                                              int ns, const int32_t *__restrict__ mask,
+                                              const int32_t *__restrict__ jcnt, const T *__restrict__ V, int64_t ld,
+                                              const T *__restrict__ w, double *__restrict__ part, int maxcols,
+                                              int cplx, int32_t *__restrict__ step_ctr) {
+    using VT = typename Pack<T>::vec;
+    constexpr int N = Pack<T>::N;
+    __shared__ double red[4][2 * DCOLS];
+    // the step counter of the cycle advances here: no other kernel of the step's rest reads the
+    // old value
+    if (step_ctr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *step_ctr += 1;
     const int s = find_sys(blkoff, ns, blockIdx.x);
     if (!mask[s]) return;
-    const int j = jcnt[s];
-    const int64_t base = off[s], np = len[s] / 2;
-    const int64_t p0 = (int64_t)(blockIdx.x - blkoff[s]) * (VCHUNK / 2);
-    const int wave = threadIdx.x >> 6;
-    double *pp = part + ((int64_t)blockIdx.x * NPW + wave) * maxcols;
-    T2 wv[PPT];
-    const T2 *wp = reinterpret_cast<const T2 *>(w + base);
+    const int j = jcnt[s], c0 = DCOLS * blockIdx.y;
+    if (c0 > j) return;
+    const int64_t base = off[s], np = len[s] / 2, chunk = dch[s] / 2;
+    const int64_t p0 = (int64_t)(blockIdx.x - blkoff[s]) * chunk, p1 = min(np, p0 + chunk);
+    const T *vc[DCOLS];
 #pragma unroll
-    for (int t = 0; t < PPT; ++t) {
-        const int64_t i = p0 + t * 256 + threadIdx.x;
-        const T2 x = wp[clampi(i, np)];
-        wv[t] = i < np ? x : T2{0, 0};  // zero weight past the end
-    }
-    // columns in groups of CG: all loads of a group are in flight together
-    for (int c0 = 0; c0 <= j; c0 += CG) {
-        T2 v[CG][PPT];
+    for (int u = 0; u < DCOLS; ++u) vc[u] = V + (int64_t)min(c0 + u, j) * ld + base;
+    double v[2 * DCOLS];
 #pragma unroll
-        for (int u = 0; u < CG; ++u) {
-            const T2 *vc = reinterpret_cast<const T2 *>(V + (int64_t)min(c0 + u, j) * ld + base);
+    for (int u = 0; u < 2 * DCOLS; ++u) v[u] = 0.0;
+    // two sets of loads in turn: one is in flight while the other is used
+    VT a, an, c[DCOLS], cn[DCOLS];
+    auto fetch = [&](int64_t i, VT &x, VT (&d)[DCOLS]) {
+        x = *reinterpret_cast<const VT *>(w + base + 2 * i);
 #pragma unroll
-            for (int t = 0; t < PPT; ++t) v[u][t] = vc[clampi(p0 + t * 256 + threadIdx.x, np)];
-        }
+        for (int u = 0; u < DCOLS; ++u) d[u] = *reinterpret_cast<const VT *>(vc[u] + 2 * i);
+    };
+    int64_t i = p0 + N * (int)threadIdx.x;
+    if (i < p1) fetch(i, a, c);
+    for (; i < p1; i += 256 * N) {
+        if (i + 256 * N < p1) fetch(i + 256 * N, an, cn);
 #pragma unroll
-        for (int u = 0; u < CG; ++u) {
-            if (c0 + u > j) break;
-            double ar = 0.0, ai = 0.0;
+        for (int q = 0; q < N; ++q) {
+            const bool in = N == 1 || i + q < p1;  // padding may hold anything
+            const double wr = in ? (double)a[2 * q] : 0.0, wi = in ? (double)a[2 * q + 1] : 0.0;
 #pragma unroll
-            for (int t = 0; t < PPT; ++t) {
-                ar += (double)v[u][t].x * (double)wv[t].x + (double)v[u][t].y * (double)wv[t].y;
-                ai += (double)v[u][t].x * (double)wv[t].y - (double)v[u][t].y * (double)wv[t].x;
+            for (int u = 0; u < DCOLS; ++u) {
+                const double cr = in ? (double)c[u][2 * q] : 0.0, ci = in ? (double)c[u][2 * q + 1] : 0.0;
+                v[2 * u] += cr * wr + ci * wi;
+                v[2 * u + 1] += cr * wi - ci * wr;
             }
-            wave_store<T>(ar, pp + 2 * (c0 + u));
-            wave_store<T>(cplx ? ai : 0.0, pp + 2 * (c0 + u) + 1);
         }
+        a = an;
+#pragma unroll
+        for (int u = 0; u < DCOLS; ++u) c[u] = cn[u];
+    }
+    // sums over the wave, halving the values a lane carries with each exchange: lane l ends up
+    // with value l / 4
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(DCOLS == 8, "four halvings leave one of 16 values per lane");
+#pragma unroll
+    for (int n = DCOLS, o = 32; n >= 1; n /= 2, o /= 2) {
+        const bool up = lane & o;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const double keep = up ? v[n + k] : v[k], send = up ? v[k] : v[n + k];
+            v[k] = keep + __shfl_xor(send, o, 64);
+        }
+    }
+    double r = v[0];
+    r += __shfl_xor(r, 2, 64);
+    r += __shfl_xor(r, 1, 64);
+    if ((lane & 3) == 0) red[wave][lane >> 2] = r;
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < 2 * DCOLS && c0 + t / 2 <= j) {
+        const double q = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+        part[(int64_t)blockIdx.x * maxcols + 2 * c0 + t] = (t & 1) && !cplx ? 0.0 : q;
     }
 }
 
-// out[s][k] (k < ncols) = sum of the partial slots of system s.  Grid (systems,
-// column chunks of 16); each wave reduces 4 columns, lanes striding over the slots.
-__global__ void k_reduce_cols(const int32_t *__restrict__ blkoff, int ns, const int32_t *__restrict__ mask,
-                              const int32_t *__restrict__ jcnt, int ncols_fixed, const double *__restrict__ part,
-                              int maxcols, double *__restrict__ out, int ldo, int accumulate) {
+// out[s][k] = sum of the partial slots of system s over its inner-product blocks.
+__global__ void __launch_bounds__(256) k_reduce_cols(const int32_t *__restrict__ blkoff, int ns,
+                                                     const int32_t *__restrict__ mask,
+                                                     const int32_t *__restrict__ jcnt, const double *__restrict__ part,
+                                                     int maxcols, double *__restrict__ out, int ldo, int accumulate) {
+    __shared__ double red[8][32];
     const int s = blockIdx.x;
     if (s >= ns || (mask && !mask[s])) return;
-    const int nc = ncols_fixed > 0 ? ncols_fixed : 2 * (jcnt[s] + 1);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int b0 = blkoff[s] * NPW, b1 = blkoff[s + 1] * NPW;
-    for (int k = 0; k < 4; ++k) {
-        const int c = blockIdx.y * 16 + wave * 4 + k;
-        if (c >= nc) break;
-        double acc = 0.0;
-        for (int b = b0 + lane; b < b1; b += 64) acc += part[(int64_t)b * maxcols + c];
-        acc = wave_sum(acc);
-        if (lane == 0) {
-            if (accumulate) out[(int64_t)s * ldo + c] += acc;
-            else out[(int64_t)s * ldo + c] = acc;
-        }
-    }
+    const int nc = 2 * (jcnt[s] + 1);
+    if ((int)blockIdx.y * 32 >= nc) return;
+    const int l = threadIdx.x & 31, r = threadIdx.x >> 5, c = blockIdx.y * 32 + l;  // 32 columns, 8 slot classes
+    double acc = 0.0;
+    if (c < nc)
+#pragma unroll 4
+        for (int b = blkoff[s] + r; b < blkoff[s + 1]; b += 8) acc += part[(int64_t)b * maxcols + c];
+    red[r][l] = acc;
+    __syncthreads();
+    if (r || c >= nc) return;
+#pragma unroll
+    for (int q = 1; q < 8; ++q) acc += red[q][l];
+    double *o = out + (int64_t)s * ldo + c;
+    *o = accumulate ? *o + acc : acc;
 }
 
-// w -= sum_c V_c h_c (complex h), plus per-wave partial ||w||^2 in column 0.
+// w -= sum_c V_c h_c (complex h), plus per-block partial ||w||^2.  h comes from hcol, or (fused)
+// from the partials of the inner products: every block sums them itself, which replaces a launch
+// where there are few of them (rule at launch_cgs_update); a system's first block then leaves the
+// sums in hcol.  The first block also leaves the step's column and flag in jcol / actc, which
+// the closing kernel reads while it changes jcnt and active.
 template <class T>
 __global__ void __launch_bounds__(256) k_cgs_update(const int64_t *__restrict__ off, const int64_t *__restrict__ len,
-                                                    const int32_t *__restrict__ blkoff, int ns,
+                                                    const int32_t *__restrict__ blkoff,
+                                                    const int32_t *__restrict__ dblkoff, int ns,
                                                     const int32_t *__restrict__ mask, const int32_t *__restrict__ jcnt,
                                                     const T *__restrict__ V, int64_t ld, T *__restrict__ w,
-                                                    const double *__restrict__ h, int ldh, double *__restrict__ part,
-                                                    int maxcols) {
-    using T2 = typename V2<T>::t;
+                                                    double *__restrict__ h, int ldh, int fused,
+                                                    const double *__restrict__ part, int maxcols,
+                                                    double *__restrict__ npart, int32_t *__restrict__ jcol,
+                                                    int32_t *__restrict__ actc) {
+    using VT = typename Pack<T>::vec;
+    constexpr int N = Pack<T>::N, R = VCHUNK / 2 / (256 * N);  // 16-byte loads per thread and column
+    static_assert(R >= 1, "chunk too small");
+    extern __shared__ double hs[];
     const int s = find_sys(blkoff, ns, blockIdx.x);
-    if (!mask[s]) return;
+    const bool first = (int)blockIdx.x == blkoff[s];
+    const bool on = mask[s];
     const int j = jcnt[s];
+    if (first && threadIdx.x == 0) {
+        jcol[s] = j;
+        actc[s] = on;
+    }
+    if (!on) return;
     const int64_t base = off[s], np = len[s] / 2;
     const int64_t p0 = (int64_t)(blockIdx.x - blkoff[s]) * (VCHUNK / 2);
-    T2 *wp = reinterpret_cast<T2 *>(w + base);
-    double xr[PPT], xi[PPT];
-#pragma unroll
-    for (int t = 0; t < PPT; ++t) {
-        const int64_t i = p0 + t * 256 + threadIdx.x;
-        const T2 v = wp[clampi(i, np)];
-        xr[t] = v.x;
-        xi[t] = v.y;
-    }
-    const double *hs = h + (int64_t)s * ldh;
-    for (int c0 = 0; c0 <= j; c0 += CG) {
-        T2 v[CG][PPT];
-#pragma unroll
-        for (int u = 0; u < CG; ++u) {
-            const T2 *vc = reinterpret_cast<const T2 *>(V + (int64_t)min(c0 + u, j) * ld + base);
-#pragma unroll
-            for (int t = 0; t < PPT; ++t) {
-                // last read of the basis in this Arnoldi step (the next step streams the
-                // preconditioner and the operator first): non-temporal
-                typedef T vec2 __attribute__((ext_vector_type(2)));
-                const vec2 q = __builtin_nontemporal_load(
-                    reinterpret_cast<const vec2 *>(vc + clampi(p0 + t * 256 + threadIdx.x, np)));
-                v[u][t] = T2{q.x, q.y};
-            }
+    double *hsys = h + (int64_t)s * ldh;
+    for (int c = threadIdx.x; c < 2 * (j + 1); c += 256) {
+        double a;
+        if (fused) {
+            a = 0.0;
+#pragma unroll 8
+            for (int b = dblkoff[s]; b < dblkoff[s + 1]; ++b) a += part[(int64_t)b * maxcols + c];
+            if (first) hsys[c] = a;
+        } else {
+            a = hsys[c];
         }
+        hs[c] = a;
+    }
+    // element r of this thread: pairs i .. i + N - 1; reads past the end stay inside the slot's
+    // padding or at the last element
+    int64_t at[R];
+    double xr[R][N], xi[R][N];
 #pragma unroll
-        for (int u = 0; u < CG; ++u) {
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = p0 + N * (r * 256 + (int64_t)threadIdx.x);
+        at[r] = i < np ? i : (np - 1) / N * N;
+        const VT v = *reinterpret_cast<const VT *>(w + base + 2 * at[r]);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            xr[r][q] = v[2 * q];
+            xi[r][q] = v[2 * q + 1];
+        }
+    }
+    // two sets of columns in turn: one is in flight while the other is used
+    VT v[UG][R], nx[UG][R];
+    auto fetch = [&](int c0, VT (&d)[UG][R]) {
+#pragma unroll
+        for (int u = 0; u < UG; ++u) {
+            const T *vc = V + (int64_t)min(c0 + u, j) * ld + base;
+            // last read of the basis in this Arnoldi step (the next step streams the
+            // preconditioner and the operator first): non-temporal
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                d[u][r] = __builtin_nontemporal_load(reinterpret_cast<const VT *>(vc + 2 * at[r]));
+        }
+    };
+    fetch(0, v);
+    __syncthreads();
+    for (int c0 = 0; c0 <= j; c0 += UG) {
+        if (c0 + UG <= j) fetch(c0 + UG, nx);
+#pragma unroll
+        for (int u = 0; u < UG; ++u) {
             if (c0 + u > j) break;
             const double hr = hs[2 * (c0 + u)], hi = hs[2 * (c0 + u) + 1];
 #pragma unroll
-            for (int t = 0; t < PPT; ++t) {
-                xr[t] -= hr * (double)v[u][t].x - hi * (double)v[u][t].y;
-                xi[t] -= hr * (double)v[u][t].y + hi * (double)v[u][t].x;
-            }
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    xr[r][q] -= hr * (double)v[u][r][2 * q] - hi * (double)v[u][r][2 * q + 1];
+                    xi[r][q] -= hr * (double)v[u][r][2 * q + 1] + hi * (double)v[u][r][2 * q];
+                }
         }
+#pragma unroll
+        for (int u = 0; u < UG; ++u)
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[u][r] = nx[u][r];
     }
     double nrm = 0.0;
 #pragma unroll
-    for (int t = 0; t < PPT; ++t) {
-        const int64_t i = p0 + t * 256 + threadIdx.x;
-        if (i < np) {
-            const T2 v{(T)xr[t], (T)xi[t]};
-            wp[i] = v;
-            nrm += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = p0 + N * (r * 256 + (int64_t)threadIdx.x);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            if (i + q >= np) break;
+            const T a = (T)xr[r][q], b = (T)xi[r][q];
+            w[base + 2 * (i + q)] = a;
+            w[base + 2 * (i + q) + 1] = b;
+            nrm += (double)a * (double)a + (double)b * (double)b;
         }
     }
-    wave_store<T>(nrm, part + ((int64_t)blockIdx.x * NPW + (threadIdx.x >> 6)) * maxcols);
+    block_store(nrm, npart + blockIdx.x);
 }
 
-// Per-wave partials of ||x||^2.
+// Per-block partials of ||x||^2.
 template <class T>
 __global__ void __launch_bounds__(256) k_norm2(const int64_t *__restrict__ off, const int64_t *__restrict__ len,
                                                const int32_t *__restrict__ blkoff, int ns,
                                                const int32_t *__restrict__ mask, const T *__restrict__ x,
-                                               double *__restrict__ part, int maxcols) {
+                                               double *__restrict__ part) {
     const int s = find_sys(blkoff, ns, blockIdx.x);
     if (mask && !mask[s]) return;
     const int64_t base = off[s], n = len[s];
@@ -570,19 +680,16 @@ __global__ void __launch_bounds__(256) k_norm2(const int64_t *__restrict__ off, 
         const double v = (double)x[base + clampi(i, n)];
         a += i < n ? v * v : 0.0;
     }
-    wave_store<T>(a, part + ((int64_t)blockIdx.x * NPW + (threadIdx.x >> 6)) * maxcols);
+    block_store(a, part + blockIdx.x);
 }
 
-// y = a_s * x (a_s = scal[s] or 1/scal[s]); optional second destination.  The last
-// kernel of an Arnoldi step also advances the step counter (step_ctr, one thread).
+// y = a_s * x (a_s = scal[s] or 1/scal[s]); optional second destination.
 template <class TI, class TO>
 __global__ void __launch_bounds__(256) k_scale(const int64_t *__restrict__ off, const int64_t *__restrict__ len,
                                                const int32_t *__restrict__ blkoff, int ns,
                                                const int32_t *__restrict__ mask, const double *__restrict__ scal,
                                                int invert, const TI *__restrict__ x, TO *__restrict__ y1,
-                                               const int32_t *__restrict__ jcol, int64_t ld1, TO *__restrict__ y2,
-                                               int32_t *__restrict__ step_ctr) {
-    if (step_ctr && blockIdx.x == 0 && threadIdx.x == 0) *step_ctr += 1;
+                                               const int32_t *__restrict__ jcol, int64_t ld1, TO *__restrict__ y2) {
     const int s = find_sys(blkoff, ns, blockIdx.x);
     if (mask && !mask[s]) return;
     const int64_t base = off[s], n = len[s];
@@ -664,19 +771,13 @@ __global__ void __launch_bounds__(256) k_axpy(const int64_t *__restrict__ off, c
     }
 }
 
-__device__ __forceinline__ double slot_sum(const double *part, int maxcols, int b0, int b1, int col) {
-    double a = 0.0;
-    for (int b = b0 * NPW + (int)threadIdx.x; b < b1 * NPW; b += blockDim.x) a += part[(int64_t)b * maxcols + col];
-    return wave_sum(a);  // blockDim.x == 64
-}
-
-// Start of a GMRES cycle (one wave per system): beta = ||r||; systems with
+// Start of a GMRES cycle (one block of 256 per system): beta = ||r||; systems with
 // beta/bnorm <= rtol stop; otherwise g = (beta, 0, ...), jcnt = 0, active = 1.  The
 // tolerance is read from device memory (the launch may be replayed from a graph); the
 // step counter of the cycle is reset; each system's running flag is also written to
 // host-visible memory (hrun, may be null).
 __global__ void k_cycle_start(int ns, const int32_t *__restrict__ blkoff, const double *__restrict__ part,
-                              int maxcols, int32_t *__restrict__ running, int32_t *__restrict__ active,
+                              int32_t *__restrict__ running, int32_t *__restrict__ active,
                               int32_t *__restrict__ jcnt, const double *__restrict__ bnorm,
                               const double *__restrict__ rtol_d, double *__restrict__ g, int m,
                               double *__restrict__ beta_out, double *__restrict__ resid_out,
@@ -693,7 +794,7 @@ __global__ void k_cycle_start(int ns, const int32_t *__restrict__ blkoff, const 
         return;
     }
     const double rtol = *rtol_d;
-    const double beta = sqrt(slot_sum(part, maxcols, blkoff[s], blkoff[s + 1], 0));
+    const double beta = sqrt(sum_partials(part, blkoff[s], blkoff[s + 1]));
     double *gs = g + (int64_t)s * 2 * (m + 1);
     for (int i = threadIdx.x; i < 2 * (m + 1); i += blockDim.x) gs[i] = 0.0;
     if (threadIdx.x != 0) return;
@@ -712,106 +813,140 @@ __global__ void k_cycle_start(int ns, const int32_t *__restrict__ blkoff, const 
     gs[0] = beta;
 }
 
-// After Arnoldi step j (one wave per system): h_{j+1,j} = ||w||, apply the previous
-// complex Givens rotations to column j of H, build the new one, update g.
+// After Arnoldi step j of a system: h_{j+1,j} = ||w||, apply the previous complex Givens rotations
+// to column j of H, build the new one, update g (one wave).
 // Rotation G = [[c, s], [-conj(s), c]] with c real: G [a; b] = [r; 0].
-__global__ void k_arnoldi_finish(int ns, const int32_t *__restrict__ blkoff, const double *__restrict__ part,
-                                 int maxcols, int32_t *__restrict__ active, int32_t *__restrict__ jcnt,
-                                 const double *__restrict__ hcol, int ldh, double *__restrict__ H,
-                                 double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ g,
-                                 double *__restrict__ hnext, const double *__restrict__ bnorm,
-                                 const double *__restrict__ rtol_d, int m, int32_t *__restrict__ iters, int max_iter,
-                                 double *__restrict__ resid_est, int32_t *__restrict__ hflags,
-                                 const int32_t *__restrict__ step_ctr, int spc, int nslots) {
-    __shared__ double colr[1025], coli[1025], csl[1024], snr[1024], sni[1024];
-    const int s = blockIdx.x;
-    if (s >= ns) return;
-    // the system's flag after this step, also written to host memory (one slot per group of
-    // spc consecutive steps: the last step of the group leaves its flag there)
-    int32_t *hf = hflags + (int64_t)((*step_ctr / spc) % nslots) * ns + s;
-    if (!active[s]) {
-        if (threadIdx.x == 0) *hf = 0;
-        return;
-    }
-    const int j = jcnt[s];
-    const double hn = sqrt(slot_sum(part, maxcols, blkoff[s], blkoff[s + 1], 0));
-    const double *hc = hcol + (int64_t)s * ldh;
-    double *css = cs + (int64_t)s * m, *sns = sn + (int64_t)s * 2 * m;
-    for (int i = threadIdx.x; i <= j; i += blockDim.x) {
-        colr[i] = hc[2 * i];
-        coli[i] = hc[2 * i + 1];
-        if (i < j) {
-            csl[i] = css[i];
-            snr[i] = sns[2 * i];
-            sni[i] = sns[2 * i + 1];
-        }
-    }
-    __syncthreads();
+// The rotated entry x_{i+1} = -conj(s_i) x_i + c_i h_{i+1} of one rotation enters the next: an
+// affine recurrence, evaluated for 64 rotations at a time as a scan over the wave (six exchanges
+// instead of a chain of 64 dependent steps; |s_i| <= 1, so the composed factors do not grow).
+__device__ __forceinline__ void arnoldi_column(int s, int ns, double hn, const double *__restrict__ hcol, int ldh,
+                                               double *__restrict__ H, double *__restrict__ cs,
+                                               double *__restrict__ sn, double *__restrict__ g, int j,
+                                               int32_t *__restrict__ active, int32_t *__restrict__ jcnt,
+                                               double *__restrict__ hnext, const double *__restrict__ bnorm,
+                                               const double *__restrict__ rtol_d, int m, int32_t *__restrict__ iters,
+                                               int max_iter, double *__restrict__ resid_est, int32_t *__restrict__ hf) {
+    const int lane = threadIdx.x & 63;
     double *gs = g + (int64_t)s * 2 * (m + 1);
-    if (threadIdx.x == 0) {
-        const double br = hn, bi = 0.0;  // entry j+1 of the column (real on input)
-        colr[j + 1] = br;
-        coli[j + 1] = bi;
-        // The rotated entry i+1 of one rotation is entry i of the next: it stays in registers,
-        // so the chain of rotations carries no LDS store-to-load round trip.
-        double xr = colr[0], xi = coli[0];
-        for (int i = 0; i < j; ++i) {
-            const double c = csl[i], sr = snr[i], si = sni[i];
-            const double ar = xr, ai = xi, cr = colr[i + 1], ci = coli[i + 1];
-            // t = c a + s b ;  b' = -conj(s) a + c b
-            colr[i] = c * ar + (sr * cr - si * ci);
-            coli[i] = c * ai + (sr * ci + si * cr);
-            xr = -(sr * ar + si * ai) + c * cr;
-            xi = -(sr * ai - si * ar) + c * ci;
-        }
-        colr[j] = xr;
-        coli[j] = xi;
-        const double ar = xr, ai = xi, bnr = colr[j + 1], bni = coli[j + 1];
-        const double na = hypot(ar, ai), nb = hypot(bnr, bni);
-        const double den = hypot(na, nb);
-        double c = 1.0, sr = 0.0, si = 0.0, rr = ar, ri = ai;
-        if (den > 0.0) {
-            if (na == 0.0) {
-                c = 0.0; sr = 1.0; si = 0.0; rr = bnr; ri = bni;  // rotation maps b to the top
-                // with a = 0: [c a + s b] = b, and -conj(s) a + c b = 0
-            } else {
-                const double ur = ar / na, ui = ai / na;  // a/|a|
-                c = na / den;
-                // s = (a/|a|) conj(b) / den
-                sr = (ur * bnr + ui * bni) / den;
-                si = (ui * bnr - ur * bni) / den;
-                rr = ur * den;
-                ri = ui * den;
+    // read ahead of the scan
+    const double gr = gs[2 * j], gi = gs[2 * j + 1], bn = bnorm[s], rtol = *rtol_d;
+    const int it = iters[s] + 1;
+    const double2 *hc = reinterpret_cast<const double2 *>(hcol + (int64_t)s * ldh);
+    double *css = cs + (int64_t)s * m;
+    double2 *sns = reinterpret_cast<double2 *>(sn + (int64_t)s * 2 * m);
+    double2 *Hs = reinterpret_cast<double2 *>(H + (int64_t)s * 2 * (m + 1) * m) + (int64_t)j * (m + 1);
+    double2 x = hc[0];  // entry i0 after the rotations before it
+    for (int i0 = 0; i0 < j; i0 += 64) {
+        const int i = i0 + lane;
+        const bool in = i < j;
+        const double c = in ? css[i] : 1.0;
+        const double2 sv = in ? sns[i] : double2{0.0, 0.0};
+        const double2 h1 = in ? hc[i + 1] : double2{0.0, 0.0};
+        // affine map of this lane: x -> a x + b (identity past the end)
+        double ar = in ? -sv.x : 1.0, ai = in ? sv.y : 0.0, br = c * h1.x, bi = c * h1.y;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double pr = __shfl_up(ar, o, 64), pi = __shfl_up(ai, o, 64);
+            const double qr = __shfl_up(br, o, 64), qi = __shfl_up(bi, o, 64);
+            if (lane >= o) {
+                br += ar * qr - ai * qi;
+                bi += ar * qi + ai * qr;
+                const double tr = ar * pr - ai * pi;
+                ai = ar * pi + ai * pr;
+                ar = tr;
             }
         }
-        css[j] = c;
-        sns[2 * j] = sr;
-        sns[2 * j + 1] = si;
-        colr[j] = rr;
-        coli[j] = ri;
-        colr[j + 1] = 0.0;
-        coli[j + 1] = 0.0;
-        // g_{j+1} = -conj(s) g_j ; g_j = c g_j
-        const double gr = gs[2 * j], gi = gs[2 * j + 1];
-        gs[2 * (j + 1)] = -(sr * gr + si * gi);
-        gs[2 * (j + 1) + 1] = -(sr * gi - si * gr);
-        gs[2 * j] = c * gr;
-        gs[2 * j + 1] = c * gi;
-        hnext[s] = hn;
-        jcnt[s] = j + 1;
-        iters[s] += 1;
-        const double est = hypot(gs[2 * (j + 1)], gs[2 * (j + 1) + 1]) / bnorm[s];
-        resid_est[s] = est;
-        const bool breakdown = !(hn > 1e-300) || !(den > 0.0);
-        const int32_t on = !(est <= *rtol_d || breakdown || j + 1 >= m || iters[s] >= max_iter || !isfinite(est));
-        active[s] = on;
-        *hf = on;
+        const double2 out{ar * x.x - ai * x.y + br, ar * x.y + ai * x.x + bi};  // x_{i+1}
+        double2 xi{__shfl_up(out.x, 1, 64), __shfl_up(out.y, 1, 64)};
+        if (lane == 0) xi = x;
+        if (in) Hs[i] = double2{c * xi.x + (sv.x * h1.x - sv.y * h1.y), c * xi.y + (sv.x * h1.y + sv.y * h1.x)};
+        x = double2{__shfl(out.x, 63, 64), __shfl(out.y, 63, 64)};
     }
-    __syncthreads();
-    double *Hs = H + (int64_t)s * 2 * (m + 1) * m + (int64_t)j * 2 * (m + 1);  // column j, complex
-    for (int i = threadIdx.x; i <= j + 1; i += blockDim.x) {
-        Hs[2 * i] = colr[i];
-        Hs[2 * i + 1] = coli[i];
+    if (lane != 0) return;
+    const double ar = x.x, ai = x.y;
+    const double na = hypot(ar, ai), nb = fabs(hn);  // entry j + 1 of the column is real
+    const double den = hypot(na, nb);
+    double c = 1.0, sr = 0.0, si = 0.0, rr = ar, ri = ai;
+    if (den > 0.0) {
+        if (na == 0.0) {
+            c = 0.0;  // rotation maps b to the top: [c a + s b] = b, -conj(s) a + c b = 0
+            sr = 1.0;
+            rr = hn;
+            ri = 0.0;
+        } else {
+            const double ur = ar / na, ui = ai / na;  // a/|a|
+            c = na / den;
+            sr = ur * hn / den;  // s = (a/|a|) conj(b) / den
+            si = ui * hn / den;
+            rr = ur * den;
+            ri = ui * den;
+        }
+    }
+    css[j] = c;
+    sns[j] = double2{sr, si};
+    Hs[j] = double2{rr, ri};
+    Hs[j + 1] = double2{0.0, 0.0};
+    // g_{j+1} = -conj(s) g_j ; g_j = c g_j
+    const double g1r = -(sr * gr + si * gi), g1i = -(sr * gi - si * gr);
+    gs[2 * (j + 1)] = g1r;
+    gs[2 * (j + 1) + 1] = g1i;
+    gs[2 * j] = c * gr;
+    gs[2 * j + 1] = c * gi;
+    hnext[s] = hn;
+    jcnt[s] = j + 1;
+    iters[s] = it;
+    const double est = hypot(g1r, g1i) / bn;
+    resid_est[s] = est;
+    const bool breakdown = !(hn > 1e-300) || !(den > 0.0);
+    const int32_t on = !(est <= rtol || breakdown || j + 1 >= m || it >= max_iter || !isfinite(est));
+    active[s] = on;
+    *hf = on;
+}
+
+// Close of an Arnoldi step, one launch: V_{j+1} = cur = w / ||w|| on the vector blocks, and the
+// column of H (arnoldi_column) on one more block per system.  The vector blocks read the step's
+// column and flag from jcol / actc, since the column blocks change jcnt and active meanwhile.
+// hflags: one slot per group of spc consecutive steps, the last step of the group leaves its
+// flag there (step_ctr counts this step already).
+template <class T>
+__global__ void __launch_bounds__(256) k_arnoldi_close(
+    const int64_t *__restrict__ off, const int64_t *__restrict__ len, const int32_t *__restrict__ blkoff, int nvb,
+    int ns, const double *__restrict__ npart, const int32_t *__restrict__ jcol, const int32_t *__restrict__ actc,
+    const T *__restrict__ w, T *__restrict__ V, int64_t ld, T *__restrict__ cur, const double *__restrict__ hcol,
+    int ldh, double *__restrict__ H, double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ g,
+    int32_t *__restrict__ active, int32_t *__restrict__ jcnt, double *__restrict__ hnext,
+    const double *__restrict__ bnorm, const double *__restrict__ rtol_d, int m, int32_t *__restrict__ iters,
+    int max_iter, double *__restrict__ resid_est, int32_t *__restrict__ hflags, const int32_t *__restrict__ step_ctr,
+    int spc, int nslots) {
+    const bool column = (int)blockIdx.x < ns;  // the column blocks first: theirs is the longer chain
+    const int vb = (int)blockIdx.x - ns;
+    const int s = column ? (int)blockIdx.x : find_sys(blkoff, ns, vb);
+    int32_t *hf = hflags + (int64_t)(((*step_ctr - 1) / spc) % nslots) * ns + s;
+    if (!actc[s]) {
+        if (column && threadIdx.x == 0) *hf = 0;
+        return;
+    }
+    const int j = jcol[s];
+    const double hn = sqrt(sum_partials(npart, blkoff[s], blkoff[s + 1]));
+    if (column) {
+        if (threadIdx.x < 64)
+            arnoldi_column(s, ns, hn, hcol, ldh, H, cs, sn, g, j, active, jcnt, hnext, bnorm, rtol_d, m, iters,
+                           max_iter, resid_est, hf);
+        return;
+    }
+    const double a = hn != 0.0 ? 1.0 / hn : 0.0;
+    const int64_t base = off[s], n = len[s];
+    const int64_t i0 = (int64_t)(vb - blkoff[s]) * VCHUNK;
+    T *d = V + base + (int64_t)(j + 1) * ld;
+#pragma unroll
+    for (int t = 0; t < VCHUNK / 512; ++t) {
+        const int64_t i = i0 + 2 * (t * 256 + (int64_t)threadIdx.x);  // a complex pair
+        if (i >= n) break;
+        using T2 = typename V2<T>::t;
+        const T2 x = *reinterpret_cast<const T2 *>(w + base + i);
+        const T2 v{(T)(a * (double)x.x), (T)(a * (double)x.y)};
+        *reinterpret_cast<T2 *>(d + i) = v;
+        *reinterpret_cast<T2 *>(cur + base + i) = v;
     }
 }
 
@@ -864,12 +999,12 @@ __global__ void k_zero_flagged(const int64_t *__restrict__ off, const int64_t *_
 
 // out[s] = sqrt(sum of partials); with bnorm: resid[s] = out/bnorm, running[s] = 0 if <= rtol.
 __global__ void k_norm_finish(int ns, const int32_t *__restrict__ blkoff, const double *__restrict__ part,
-                              int maxcols, const int32_t *__restrict__ mask, double *__restrict__ out,
+                              const int32_t *__restrict__ mask, double *__restrict__ out,
                               const double *__restrict__ bnorm, double rtol, double *__restrict__ resid,
                               int32_t *__restrict__ running) {
     const int s = blockIdx.x;
     if (s >= ns || (mask && !mask[s])) return;
-    const double nrm = sqrt(slot_sum(part, maxcols, blkoff[s], blkoff[s + 1], 0));
+    const double nrm = sqrt(sum_partials(part, blkoff[s], blkoff[s + 1]));
     if (threadIdx.x != 0) return;
     out[s] = nrm;
     if (bnorm) {
@@ -885,31 +1020,34 @@ __global__ void k_norm_finish(int ns, const int32_t *__restrict__ blkoff, const 
 
 template <class T>
 void launch_dots(const Batch &B, const int32_t *mask, const int32_t *jcnt, const T *V, int64_t ld, const T *w,
-                 double *part, int cplx, hipStream_t st) {
+                 double *part, int cplx, int32_t *step_ctr, hipStream_t st) {
     VGUARD(B);
-    k_dots<T><<<VGRID(B.vs)>>>(B.off.p, B.len.p, B.vs.blkoff.p, B.ns, mask, jcnt, V, ld, w, part, B.maxcols, cplx);
+    const dim3 grid(B.ds.nblocks, (B.maxcols / 2 + DCOLS - 1) / DCOLS);
+    k_dots<T><<<grid, 256, 0, st>>>(B.off.p, B.len.p, B.dch.p, B.ds.blkoff.p, B.ns, mask, jcnt, V, ld, w, part,
+                                    B.maxcols, cplx, step_ctr);
     THM_HIP(hipGetLastError());
 }
 template <class T>
 void launch_cgs_update(const Batch &B, const int32_t *mask, const int32_t *jcnt, const T *V, int64_t ld, T *w,
-                       const double *h, int ldh, double *part, hipStream_t st) {
+                       double *h, int ldh, bool fused, const double *part, double *npart, int32_t *jcol,
+                       int32_t *actc, hipStream_t st) {
     VGUARD(B);
-    k_cgs_update<T><<<VGRID(B.vs)>>>(B.off.p, B.len.p, B.vs.blkoff.p, B.ns, mask, jcnt, V, ld, w, h, ldh, part,
-                                     B.maxcols);
+    k_cgs_update<T><<<B.vs.nblocks, 256, sizeof(double) * B.maxcols, st>>>(
+        B.off.p, B.len.p, B.vs.blkoff.p, B.ds.blkoff.p, B.ns, mask, jcnt, V, ld, w, h, ldh, fused ? 1 : 0, part,
+        B.maxcols, npart, jcol, actc);
     THM_HIP(hipGetLastError());
 }
 template <class T>
 void launch_norm2(const Batch &B, const int32_t *mask, const T *x, double *part, hipStream_t st) {
     VGUARD(B);
-    k_norm2<T><<<VGRID(B.vs)>>>(B.off.p, B.len.p, B.vs.blkoff.p, B.ns, mask, x, part, B.maxcols);
+    k_norm2<T><<<VGRID(B.vs)>>>(B.off.p, B.len.p, B.vs.blkoff.p, B.ns, mask, x, part);
     THM_HIP(hipGetLastError());
 }
 template <class TI, class TO>
 void launch_scale(const Batch &B, const int32_t *mask, const double *scal, int invert, const TI *x, TO *y1,
-                  const int32_t *jcol, int64_t ld1, TO *y2, hipStream_t st, int32_t *step_ctr) {
+                  const int32_t *jcol, int64_t ld1, TO *y2, hipStream_t st) {
     VGUARD(B);
-    k_scale<TI, TO><<<VGRID(B.vs)>>>(B.off.p, B.len.p, B.vs.blkoff.p, B.ns, mask, scal, invert, x, y1, jcol, ld1, y2,
-                                     step_ctr);
+    k_scale<TI, TO><<<VGRID(B.vs)>>>(B.off.p, B.len.p, B.vs.blkoff.p, B.ns, mask, scal, invert, x, y1, jcol, ld1, y2);
     THM_HIP(hipGetLastError());
 }
 template <class T>
@@ -927,33 +1065,33 @@ void launch_axpy(const Batch &B, const int32_t *mask, const double *scal, const 
 }
 void launch_norm_finish(const Batch &B, const double *part, const int32_t *mask, double *out, const double *bnorm,
                         double rtol, double *resid, int32_t *running, hipStream_t st) {
-    k_norm_finish<<<B.ns, 64, 0, st>>>(B.ns, B.vs.blkoff.p, part, B.maxcols, mask, out, bnorm, rtol,
+    k_norm_finish<<<B.ns, 256, 0, st>>>(B.ns, B.vs.blkoff.p, part, mask, out, bnorm, rtol,
                                                    resid, running);
     THM_HIP(hipGetLastError());
 }
-void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt, int ncols_fixed,
-                        const double *part, double *out, int ldo, int accumulate, hipStream_t st) {
-    const int chunks = ncols_fixed > 0 ? (ncols_fixed + 15) / 16 : (B.maxcols + 15) / 16;
-    k_reduce_cols<<<dim3(B.ns, chunks), 256, 0, st>>>(B.vs.blkoff.p, B.ns, mask, jcnt, ncols_fixed, part, B.maxcols, out, ldo,
-                                       accumulate);
+void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt, const double *part, double *out,
+                        int ldo, int accumulate, hipStream_t st) {
+    k_reduce_cols<<<dim3(B.ns, (B.maxcols + 31) / 32), 256, 0, st>>>(B.ds.blkoff.p, B.ns, mask, jcnt, part,
+                                                                      B.maxcols, out, ldo, accumulate);
     THM_HIP(hipGetLastError());
 }
 void launch_cycle_start(const Batch &B, const double *part, int32_t *running, int32_t *active, int32_t *jcnt,
                         const double *bnorm, const double *rtol_d, double *g, int m, double *beta, double *resid,
                         int32_t *iters, int max_iter, int32_t *step_ctr, int32_t *hrun, hipStream_t st) {
-    k_cycle_start<<<B.ns, 64, 0, st>>>(B.ns, B.vs.blkoff.p, part, B.maxcols, running, active, jcnt, bnorm, rtol_d,
+    k_cycle_start<<<B.ns, 256, 0, st>>>(B.ns, B.vs.blkoff.p, part, running, active, jcnt, bnorm, rtol_d,
                                        g, m, beta, resid, iters, max_iter, step_ctr, hrun);
     THM_HIP(hipGetLastError());
 }
-void launch_arnoldi_finish(const Batch &B, const double *part, int32_t *active, int32_t *jcnt, const double *hcol,
-                           int ldh, double *H, double *cs, double *sn, double *g, double *hnext,
-                           const double *bnorm, const double *rtol_d, int m, int32_t *iters, int max_iter,
-                           double *est, int32_t *hflags, const int32_t *step_ctr, int spc, int nslots,
-                           hipStream_t st) {
+template <class T>
+void launch_arnoldi_close(const Batch &B, const double *npart, const int32_t *jcol, const int32_t *actc, const T *w,
+                          T *V, int64_t ld, T *cur, const double *hcol, int ldh, double *H, double *cs, double *sn,
+                          double *g, int32_t *active, int32_t *jcnt, double *hnext, const double *bnorm,
+                          const double *rtol_d, int m, int32_t *iters, int max_iter, double *est, int32_t *hflags,
+                          const int32_t *step_ctr, int spc, int nslots, hipStream_t st) {
     if (m > 1024) fail(THM_EINVAL, "restart must be <= 1024");
-    k_arnoldi_finish<<<B.ns, 64, 0, st>>>(B.ns, B.vs.blkoff.p, part, B.maxcols, active, jcnt, hcol,
-                                                      ldh, H, cs, sn, g, hnext, bnorm, rtol_d, m, iters, max_iter,
-                                                      est, hflags, step_ctr, spc, nslots);
+    k_arnoldi_close<T><<<B.vs.nblocks + B.ns, 256, 0, st>>>(
+        B.off.p, B.len.p, B.vs.blkoff.p, B.vs.nblocks, B.ns, npart, jcol, actc, w, V, ld, cur, hcol, ldh, H, cs, sn, g,
+        active, jcnt, hnext, bnorm, rtol_d, m, iters, max_iter, est, hflags, step_ctr, spc, nslots);
     THM_HIP(hipGetLastError());
 }
 void launch_hsolve(const Batch &B, const int32_t *running, const int32_t *jcnt, const double *H, const double *g,
@@ -968,25 +1106,31 @@ void launch_zero_flagged(const Batch &B, const uint8_t *const *dirs, T *x, hipSt
     THM_HIP(hipGetLastError());
 }
 
-#define INST_T(T)                                                                                            \
-    template void launch_dots<T>(const Batch &, const int32_t *, const int32_t *, const T *, int64_t,         \
-                                 const T *, double *, int, hipStream_t);                                     \
-    template void launch_cgs_update<T>(const Batch &, const int32_t *, const int32_t *, const T *, int64_t,   \
-                                       T *, const double *, int, double *, hipStream_t);                     \
+#define INST_T(T)                                                                                             \
+    template void launch_dots<T>(const Batch &, const int32_t *, const int32_t *, const T *, int64_t, const T *,   \
+                                 double *, int, int32_t *, hipStream_t);                                      \
+    template void launch_cgs_update<T>(const Batch &, const int32_t *, const int32_t *, const T *, int64_t, T *,   \
+                                       double *, int, bool, const double *, double *, int32_t *, int32_t *,   \
+                                       hipStream_t);                                                          \
+    template void launch_arnoldi_close<T>(const Batch &, const double *, const int32_t *, const int32_t *,    \
+                                          const T *, T *, int64_t, T *, const double *, int, double *, double *,   \
+                                          double *, double *, int32_t *, int32_t *, double *, const double *, \
+                                          const double *, int, int32_t *, int, double *, int32_t *,           \
+                                          const int32_t *, int, int, hipStream_t);                            \
     template void launch_norm2<T>(const Batch &, const int32_t *, const T *, double *, hipStream_t);          \
     template void launch_lincomb<T>(const Batch &, const int32_t *, const int32_t *, const T *, int64_t,      \
-                                    const double *, int, T *, hipStream_t);                                  \
+                                    const double *, int, T *, hipStream_t);                                   \
     template void launch_zero_flagged<T>(const Batch &, const uint8_t *const *, T *, hipStream_t);
 INST_T(double)
 INST_T(float)
 template void launch_scale<double, double>(const Batch &, const int32_t *, const double *, int, const double *,
-                                           double *, const int32_t *, int64_t, double *, hipStream_t, int32_t *);
+                                           double *, const int32_t *, int64_t, double *, hipStream_t);
 template void launch_scale<float, float>(const Batch &, const int32_t *, const double *, int, const float *,
-                                         float *, const int32_t *, int64_t, float *, hipStream_t, int32_t *);
+                                         float *, const int32_t *, int64_t, float *, hipStream_t);
 template void launch_scale<float, double>(const Batch &, const int32_t *, const double *, int, const float *,
-                                          double *, const int32_t *, int64_t, double *, hipStream_t, int32_t *);
+                                          double *, const int32_t *, int64_t, double *, hipStream_t);
 template void launch_scale<double, float>(const Batch &, const int32_t *, const double *, int, const double *,
-                                          float *, const int32_t *, int64_t, float *, hipStream_t, int32_t *);
+                                          float *, const int32_t *, int64_t, float *, hipStream_t);
 template void launch_axpy<double, double>(const Batch &, const int32_t *, const double *, const double *, double *,
                                           hipStream_t);
 template void launch_axpy<float, float>(const Batch &, const int32_t *, const double *, const float *, float *,

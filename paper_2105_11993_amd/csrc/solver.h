@@ -107,10 +107,11 @@ namespace thm {
 struct Krylov {
     Batch B;
     int m = 50;
-    DBuf<double> H, cs, sn, g, y, hcol, hcol2, hnext, bnorm, beta, resid, est, part;
+    DBuf<double> H, cs, sn, g, y, hcol, hcol2, hnext, bnorm, beta, resid, est, part, npart;
     DBuf<double> rtol_d;  // Arnoldi stopping tolerance, read by the (captured) finish kernel
     double rtol_h = 0.0;  // host copy (source of the async upload; lives with the workspace)
     DBuf<int32_t> running, active, jcnt, iters;
+    DBuf<int32_t> jcol, actc;   // column and flag of the step at hand (see k_arnoldi_close)
     DBuf<double> V64, w64, z64, cur64;
     DBuf<float> V32, w32, z32, cur32;
     // preconditioned basis Z = P^{-1} V (m columns), kept when the preconditioner is costly

@@ -615,7 +615,7 @@ static void build_ddm(thm_system &G, hipStream_t st) {
     D->gdir.upload(std::vector<const uint8_t *>{G.dir_d.p}, st);
     D->gres.alloc(2 * G.n);
     D->gr2.alloc(2 * G.n);
-    D->gpart.alloc((size_t)std::max(1, D->Bg.vs.nblocks) * NPW * D->Bg.maxcols);
+    D->gpart.alloc(std::max(1, D->Bg.vs.nblocks));
     D->gnorm.alloc(2);
     D->Eg.alloc(2 * G.n);
     D->minus1.upload(std::vector<double>{-1.0}, st);
