@@ -423,16 +423,16 @@ void Ctx::build_groups() {
 }
 
 template <class T>
-void Ctx::spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float csign) {
+void Ctx::spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float csign, hipStream_t on) {
     const MatDesc *m = sizeof(T) == 8 ? mat64.p : mat32.p;
     if (v == SPMV_SELL_GROUP || v == SPMV_SELL_GROUP_IL) {  // outside an Arnoldi step: per-system x
-        launch_spmv_group<T>(m, K.B.off.p, sgroups.p, gsched, ngroups, mask, x, y, b, csign, st);
+        launch_spmv_group<T>(m, K.B.off.p, sgroups.p, gsched, ngroups, mask, x, y, b, csign, on);
         return;
     }
-    launch_spmv<T>(v, m, K.B.off.p, K.B.spmv_sched(v, st), ns, mask, x, y, b, csign, st);
+    launch_spmv<T>(v, m, K.B.off.p, K.B.spmv_sched(v, st), ns, mask, x, y, b, csign, on);
 }
-template void Ctx::spmv<double>(int, const int32_t *, const double *, double *, const double *, float);
-template void Ctx::spmv<float>(int, const int32_t *, const float *, float *, const float *, float);
+template void Ctx::spmv<double>(int, const int32_t *, const double *, double *, const double *, float, hipStream_t);
+template void Ctx::spmv<float>(int, const int32_t *, const float *, float *, const float *, float, hipStream_t);
 
 static void nd_maps(PrecDesc &d, const NdPlan &p) {
     d.nd = 1;
@@ -765,6 +765,9 @@ void Ctx::build_nd_tasks(bool f64, std::vector<NdLaunch> &out) {
         L.tasks.upload(tasks, st);
         THM_HIP(hipStreamSynchronize(st));
         bcr_bytes[f64 ? 0 : 1].push_back((double)sz * (elems + vecs));
+        if (std::getenv("THM_PROGRESS"))
+            std::fprintf(stderr, "[thm]   apply %s, tree phase %zu: %d blocks, %.2f MB (%s)\n", fwd ? "up" : "down", q,
+                         L.nblocks, bcr_bytes[f64 ? 0 : 1].back() * 1e-6, f64 ? "FP64" : "FP32");
         out.push_back(std::move(L));
     };
     for (size_t q = 0; q < np; ++q)

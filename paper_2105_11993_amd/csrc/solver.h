@@ -212,7 +212,11 @@ struct Ctx {
     void ensure_xi(bool f32);  // allocates (and zeroes) the interleaved copy of one precision
     void build_groups();
     // y = A x or y = b - A x with SpMV variant v (a code of launch_spmv or SPMV_SELL_GROUP)
-    template <class T> void spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float csign);
+    template <class T>
+    void spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float csign, hipStream_t on);
+    template <class T> void spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float csign) {
+        spmv<T>(v, mask, x, y, b, csign, st);
+    }
 
     bool prec_ready = false;
     // factor groups of the batch in order of first appearance, their members, and where their
