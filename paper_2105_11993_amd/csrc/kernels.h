@@ -361,7 +361,7 @@ struct InvDesc {
     int n;
     double *A, *W;             // input A (n x n, overwritten); W is scratch (n x n)
     double *out;               // final inverse (n x n, leading dimension ldo)
-    int32_t *piv;              // 2n: pivot rows, then the column permutation
+    int32_t *piv;              // 2n: pivot rows (the column permutation at the end), row order
     int ldo;
 };
 // Batched Gauss-Jordan inversion with partial pivoting in panels of 64 columns and rank-64
