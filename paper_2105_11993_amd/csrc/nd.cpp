@@ -58,14 +58,17 @@ std::vector<Entity> entities(const Topo &t) {
     return out;
 }
 
-// Estimated seconds of one application and of the factorisation of a node, for the choice of
-// phases: a launch costs about 5 us in a replayed graph, the matrices stream at about 3.5 TB/s
-// (FP64), and the factorisation (2 us per column of the widest front, FP64 products at 10
+// Estimated seconds of one application and of the factorisation, for the choice of phases: a
+// launch takes about 6 us in a replayed graph where its matrices are small (64^2 cells of degree
+// 2: 4.8 to 7 us for phases of 2 to 10 MB), the matrices stream at about 5 TB/s (62 MB in 14 us, 479
+// in 88), and the factorisation (2 us per column of the widest front, FP64 products at 10
 // TFLOP/s) is shared by about 200 applications, one or two solves.
-constexpr double ND_LAUNCH_S = 5e-6, ND_BYTES_S = 3.5e12, ND_COL_S = 2e-6, ND_FLOP_S = 1e13, ND_REUSE = 200;
-// A phase that starts at a level of class 1 costs as much more as the refinement steps that an FP32
-// solve then needs; class 2 is only taken where no other split is possible.
-constexpr double ND_AVOID_S[3] = {0.0, 15e-6, 1.0};
+constexpr double ND_LAUNCH_S = 6e-6, ND_BYTES_S = 5e12, ND_COL_S = 2e-6, ND_FLOP_S = 1e13, ND_REUSE = 200;
+// What a level that a phase starts at adds to the cost, by its class, as a part of the cheapest
+// plan's seconds: the errors of such levels multiply, and an FP32 solve takes more refinement steps
+// or has to be finished in FP64.  (16^3 cells of degree 1 at w = 15, growth 20 to 190 on every
+// level: 8 levels started at 364 us an application, 5 in 486 us; a mixed solve 220 and 175 ms.)
+constexpr double ND_CLASS_COST[ND_CLASSES] = {0.0, 0.33, 0.6, 3.0};
 
 }  // namespace
 
@@ -145,13 +148,11 @@ void nd_plan_mesh(const Topo &t, NdPlan &P) {
         }
     }
     // phases: cheapest split of the levels, from the root down
-    std::vector<double> best(D + 1, 0.0);
-    std::vector<int> cut(D + 1, D);
-    for (int a = D - 1; a >= 0; --a) {
+    std::vector<std::vector<double>> seconds(D, std::vector<double>(D + 1, 0.0));  // of a phase [a, z)
+    for (int a = 0; a < D; ++a) {
         std::vector<int64_t> own(nbox[a], 0), bnd(nbox[a], 0);
         for (int q = 0; q < nbox[a]; ++q)
             for (int l = 0; l < a; ++l) bnd[q] += hist[a][(size_t)q * D + l];
-        best[a] = -1.0;
         for (int z = a + 1; z <= std::min(D, a + ND_MERGE); ++z) {
             double words = 0.0, flops = 0.0, wide = 0.0;
             for (int q = 0; q < nbox[a]; ++q) {
@@ -161,14 +162,26 @@ void nd_plan_mesh(const Topo &t, NdPlan &P) {
                 flops += 2.0 * b * b * b + 2.0 * b * b * c + 2.0 * b * c * c;
                 wide = std::max(wide, b);
             }
-            const double s = (a > 0 && a < ND_LEVELS ? ND_AVOID_S[std::min<int>((P.avoid >> (2 * a)) & 3u, 2)] : 0.0) +
-                             (a > 0 ? 2.0 : 1.0) * ND_LAUNCH_S + 8.0 * words / ND_BYTES_S +
-                             (wide * ND_COL_S + flops / ND_FLOP_S) / ND_REUSE + best[z];
-            if (best[a] < 0.0 || s < best[a]) {
-                best[a] = s;
-                cut[a] = z;
-            }
+            seconds[a][z] = (a > 0 ? 2.0 : 1.0) * ND_LAUNCH_S + 8.0 * words / ND_BYTES_S +
+                            (wide * ND_COL_S + flops / ND_FLOP_S) / ND_REUSE;
         }
+    }
+    auto level_class = [&](int a) { return a > 0 && a < ND_LEVELS ? (int)((P.avoid >> (2 * a)) & 3u) : 0; };
+    std::vector<int> cut(D + 1, D);
+    double least = 0.0;  // seconds of the cheapest plan, whatever its levels
+    for (bool weigh : {false, true}) {
+        std::vector<double> best(D + 1, -1.0);
+        best[D] = 0.0;
+        for (int a = D - 1; a >= 0; --a)
+            for (int z = a + 1; z <= std::min(D, a + ND_MERGE); ++z) {
+                const double s = seconds[a][z] + best[z] + (weigh ? ND_CLASS_COST[level_class(a)] * least : 0.0);
+                if (best[a] < 0.0 || s < best[a]) {
+                    best[a] = s;
+                    cut[a] = z;
+                }
+            }
+        least = best[0];
+        if (!P.avoid || P.avoid == ND_PROBE) break;
     }
     std::vector<int> from;  // first level of each phase, root first
     for (int a = 0; a < D; a = P.avoid == ND_PROBE ? a + 1 : cut[a]) from.push_back(a);

@@ -22,8 +22,9 @@ constexpr int ND_RT = 16;       // rows of a matrix tile
 constexpr int ND_KS = 16;       // columns are padded to this
 // A node whose box is close to a resonance of its own (its F_oo nearly singular) has a large G,
 // and its rounding errors grow with it; entries of G stay near 1 to 2 otherwise.  Levels are
-// classed by their largest entry: 0 up to ND_GROWTH[0], 1 up to ND_GROWTH[1], 2 beyond.
-constexpr double ND_GROWTH[2] = {3.0, 12.0};
+// classed by their largest entry: 0 up to ND_GROWTH[0], 1 up to ND_GROWTH[1] and so on.
+constexpr int ND_CLASSES = 4;
+constexpr double ND_GROWTH[ND_CLASSES - 1] = {3.0, 12.0, 100.0};
 constexpr int ND_LEVELS = 32;
 
 struct NdNode {

@@ -536,8 +536,11 @@ static void setup_nd(const std::vector<thm_system *> &reps, const std::vector<st
         const NdPlan &p = *probe[at[t]].plan;
         for (size_t q = 0; q < p.ph.size(); ++q) {
             const double v = growth[ND_LEVELS * t + q];
-            const uint64_t cls = !(v <= ND_GROWTH[1]) ? 2 : v > ND_GROWTH[0] ? 1 : 0;
+            uint64_t cls = 0;
+            while (cls + 1 < ND_CLASSES && !(v <= ND_GROWTH[cls])) ++cls;
             if (p.from[q] > 0 && p.from[q] < ND_LEVELS) avoid[at[t]] |= cls << (2 * p.from[q]);
+            if (std::getenv("THM_PROGRESS"))
+                std::fprintf(stderr, "[thm]   tree level %d: growth %.3g\n", p.from[q], v);
         }
     }
     jobs.clear();
