@@ -13,9 +13,10 @@
 // A panel itself is treated the same way in strips of 16 columns and fewer: one block per matrix
 // holds a strip of all rows in registers and eliminates it column by column (pivot search over
 // the rows not yet pivoted, swap, elimination; two barriers a column), the strip's swaps go to the
-// rest of the rows, and the panel's other columns receive a product of the strip's rank.  What bounds it is
-// the chain of columns: one launch a strip against four a column.  A front of 1572 columns:
-// @@FIG@@
+// rest of the rows, and the panel's other columns receive a product of the strip's rank.  What
+// bounds it is the chain of columns, about 2 us each, against four launches a column.  FP64:
+// sixteen matrices of 192 columns 2.6 -> 0.75 ms, one of 1572 22.4 -> 8.0 ms, one of 5800 119 -> 79
+// ms, of which 22 are the rank-64 products.
 #include "kernels.h"
 
 namespace thm {
