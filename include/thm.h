@@ -309,6 +309,10 @@ thm_status thm_time_spmv_systems(int32_t nsys, thm_system *const *sys, int32_t p
  * the Arnoldi step the batch uses code 20.  The same bits as code 20.  thm_time_spmv_batch
  * times the product alone on the copy's current contents. */
 #define THM_SPMV_SELL_GROUP_IL 29
+/* Product from the cells (code 30): the cells' two reference matrices applied on the matrix cores,
+ * 1 / mu and -w^2 eps as factors of x, without the assembled K; systems with the same K form
+ * groups as in code 20.  Not for subdomains whose transmission factor has Im s != 0. */
+#define THM_SPMV_CELLS 30
 
 /* Pin the SpMV variant of the single-system context of `sys` (the one used by
  * thm_gmres_solve on {sys}, thm_apply_operator and thm_time_spmv) and, once a DDM solve

@@ -71,7 +71,9 @@ EXPORTS = ["thm_default_opts", "thm_assemble", "thm_gmres_solve", "thm_ddm_solve
 THM_SPMV_SELL = 19
 THM_SPMV_SELL_GROUP = 20
 THM_SPMV_SELL_GROUP_IL = 29  # timing code of the grouped product on the member-interleaved copy
-SPMV_VARIANTS = [21, 41, 81, 161, 321, 641, 24, 44, 84, 164, 324, THM_SPMV_SELL, THM_SPMV_SELL_GROUP]
+THM_SPMV_CELLS = 30  # product from the cells' reference matrices
+SPMV_VARIANTS = [21, 41, 81, 161, 321, 641, 24, 44, 84, 164, 324, THM_SPMV_SELL, THM_SPMV_SELL_GROUP,
+                 THM_SPMV_CELLS]
 
 
 def load_library(path=LIB_PATH):

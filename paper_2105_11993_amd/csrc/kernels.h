@@ -48,6 +48,20 @@ struct SpmvGroup {
     // lies at xoff + r npad + j, so one row of K meets every member's value in one contiguous run
     int64_t xoff;
 };
+// Product from the cells' reference matrices instead of the assembled K (kernels_cell.hip)
+constexpr int SPMV_CELLS = 30;
+struct CellDesc {                    // one group of systems with the same K
+    int32_t nl, ne, nskel, tiles;    // functions of a cell, those not interior; DoFs not interior; wave tiles
+    int64_t ncells, zoff;            // zoff: complex entries of z before this group
+    const double *frag64;            // reference matrices in operand order
+    const float *frag32;
+    const int32_t *idx;              // ncells x ne DoFs, -1 on Dirichlet sides
+    const double *mu, *eps;          // eps may be null (1)
+    double w2;
+    const int32_t *d2c_ptr, *d2c_src;  // DoF -> cell * nl + function
+    const uint8_t *dir;
+};
+inline int cell_frag_size(int nl) { return 2 * ((nl + 15) / 16) * ((nl + 3) / 4) * 64; }
 // Host: SELL-64 layout of a CSR pattern; src[e] = CSR index of entry e, or -1 (padding).
 void sell_build(int64_t n, const std::vector<int32_t> &rowptr, const std::vector<int32_t> &col,
                 std::vector<int32_t> &ptr, std::vector<int32_t> &scol, std::vector<int32_t> &src,
@@ -74,6 +88,21 @@ struct Sched {
         blkoff.upload(all, st);
     }
 };
+
+// What the product from the cells keeps for the groups of a batch.
+struct CellBatch {
+    DBuf<CellDesc> desc;
+    DBuf<double> frag64, z;  // z: 2 scalars of either precision per (member, cell, function not interior)
+    DBuf<float> frag32;
+    DBuf<int32_t> idx;
+    Sched tiles, rows;
+    int rounds = 1, frag_max = 0;
+};
+void launch_cell_setup(int64_t ncells, int nl, int ne, const double *ref, const int32_t *dofs, const uint8_t *dir,
+                       double *frag64, float *frag32, int32_t *idx, hipStream_t st);
+template <class T>
+void launch_spmv_cells(const CellBatch &C, const MatDesc *mats, const SpmvGroup *groups, const int64_t *off,
+                       const int32_t *mask, const T *x, T *y, const T *b, float csign, hipStream_t st);
 
 // A batch of independent systems sharing kernel launches.
 struct Batch {

@@ -429,10 +429,87 @@ void Ctx::spmv(int v, const int32_t *mask, const T *x, T *y, const T *b, float c
         launch_spmv_group<T>(m, K.B.off.p, sgroups.p, gsched, ngroups, mask, x, y, b, csign, on);
         return;
     }
+    if (v == SPMV_CELLS) {
+        launch_spmv_cells<T>(cells, m, sgroups.p, K.B.off.p, mask, x, y, b, csign, on);
+        return;
+    }
     launch_spmv<T>(v, m, K.B.off.p, K.B.spmv_sched(v, st), ns, mask, x, y, b, csign, on);
 }
 template void Ctx::spmv<double>(int, const int32_t *, const double *, double *, const double *, float, hipStream_t);
 template void Ctx::spmv<float>(int, const int32_t *, const float *, float *, const float *, float, hipStream_t);
+
+// Interface sides with Im s != 0 add to K; a system of 2^28 pairs of cell and member is left to
+// the assembled forms (32-bit pair indices).
+bool Ctx::ensure_cells() {
+    if (cells.desc.n) return true;
+    for (const SpmvGroup &G : hgroups) {
+        const thm_system &S = *sys[G.rep];
+        if (S.iface_sides && S.prob.transmission[1] != 0.0) return false;
+        if (S.topo.n_cells * G.nm >= (int64_t(1) << 28) || S.n >= (int64_t(1) << 30)) return false;
+    }
+    CellBatch &C = cells;
+    std::vector<CellDesc> h(ngroups);
+    std::vector<int64_t> tiles(ngroups), rows(ngroups);
+    int64_t nf = 0, ni = 0, nz = 0, nt = 0;
+    for (int g = 0; g < ngroups; ++g) {
+        const SpmvGroup &G = hgroups[g];
+        const Topo &t = sys[G.rep]->topo;
+        CellDesc &d = h[g];
+        d.nl = t.n_loc;
+        d.ne = t.n_loc - t.n_int;
+        d.nskel = (int32_t)t.cell_off;
+        d.ncells = t.n_cells;
+        d.zoff = nz;
+        tiles[g] = d.tiles = (int32_t)((t.n_cells * G.nm + 7) / 8);
+        rows[g] = (int64_t)d.nskel * G.nm;
+        nt += tiles[g];
+        nf += cell_frag_size(d.nl);
+        ni += t.n_cells * d.ne;
+        nz += t.n_cells * G.nm * d.ne;
+        C.frag_max = std::max(C.frag_max, cell_frag_size(d.nl));
+    }
+    C.frag64.alloc(nf);
+    C.frag32.alloc(nf);
+    C.idx.alloc(std::max<int64_t>(ni, 1));
+    C.z.alloc(std::max<int64_t>(2 * nz, 1));
+    nf = ni = 0;
+    for (int g = 0; g < ngroups; ++g) {
+        thm_system &S = *sys[hgroups[g].rep];
+        CellDesc &d = h[g];
+        d.frag64 = C.frag64.p + nf;
+        d.frag32 = C.frag32.p + nf;
+        d.idx = C.idx.p + ni;
+        d.mu = S.mu_d.p;
+        d.eps = S.eps_d.n ? S.eps_d.p : nullptr;
+        d.w2 = S.prob.omega * S.prob.omega;
+        d.d2c_ptr = S.d2c_ptr.p;
+        d.d2c_src = S.d2c_src.p;
+        d.dir = S.dir_d.p;
+        launch_cell_setup(d.ncells, d.nl, d.ne, S.tcell.ref.p, S.cell_dofs.p, d.dir, C.frag64.p + nf, C.frag32.p + nf,
+                          C.idx.p + ni, st);
+        nf += cell_frag_size(d.nl);
+        ni += d.ncells * d.ne;
+    }
+    C.rounds = (int)std::max<int64_t>(1, nt / (4 * 2048));
+    C.tiles.build(tiles, 4 * C.rounds, st);
+    C.rows.build(rows, 256, st);
+    C.desc.upload(h, st);
+    THM_HIP(hipStreamSynchronize(st));
+    return true;
+}
+
+double Ctx::cell_bytes(double w) const {
+    double by = 0.0;
+    for (const SpmvGroup &G : hgroups) {
+        const thm_system &S = *sys[G.rep];
+        const double nc = (double)S.topo.n_cells, ne = S.topo.n_loc - S.topo.n_int;
+        by += nc * (4.0 * 2.0 * ne + 8.0) + 4.0 * (double)(S.topo.cell_off + 1);  // both index lists, mu
+        for (int j = 0; j < G.nm; ++j)  // x, y, z both ways, C
+            by += 4.0 * w * ((double)S.n + nc * ne) + (w + 4.0) * (double)sys[G.mem[j]]->C.col.size() +
+                  4.0 * (double)S.topo.cell_off;
+    }
+    return by;
+}
 
 static void nd_maps(PrecDesc &d, const NdPlan &p) {
     d.nd = 1;
@@ -1399,8 +1476,12 @@ static void tune_store() {
 void Ctx::autotune() {
     std::vector<int> cand = {21, 41, 81, 161, 321, 24, 44, 84, 164, 324, SPMV_SELL};
     if (spmv_shared) cand.push_back(SPMV_SELL_GROUP);
-    for (int c : cand)
-        if (c != SPMV_SELL_GROUP) K.B.spmv_sched(c, st);
+    auto ready = [&](int v) {  // the variant, with what it needs in place
+        if (v == SPMV_CELLS && ensure_cells()) return v;
+        if (v == SPMV_CELLS) v = SPMV_SELL;
+        if (v != SPMV_SELL_GROUP) K.B.spmv_sched(v, st);
+        return v;
+    };
     int64_t nnz = 0, nrows = 0;
     for (thm_system *s : sys) {
         nnz += (int64_t)s->K.col.size();
@@ -1417,12 +1498,15 @@ void Ctx::autotune() {
         tune_load();
         auto a = g_tune.find(key64), b = g_tune.find(key32);
         if (a != g_tune.end() && b != g_tune.end()) {
-            lpr64 = a->second;
-            lpr32 = b->second;
+            lpr64 = ready(a->second);
+            lpr32 = ready(b->second);
             return;
         }
     }
-    (void)nnz;
+    // below about 3 million entries (times members) its two launches lose to the one of the assembled
+    // forms: 64^2 cells of degree 2 in FP64 (2.2 M) 9.2 us against 8.5, 60^2 of degree 3 (5 M) 12 against 16
+    if (nnz >= 3000000 && ensure_cells()) cand.push_back(SPMV_CELLS);
+    for (int c : cand) ready(c);
     hipEvent_t e0, e1;
     THM_HIP(hipEventCreate(&e0));
     THM_HIP(hipEventCreate(&e1));

@@ -204,6 +204,9 @@ struct Ctx {
     DBuf<uint8_t> sgcrow;
     Sched gsched;
     int ngroups = 0;
+    CellBatch cells;         // of the product from the cells (SPMV_CELLS); built on first use
+    bool ensure_cells();     // false: some system's K holds more than its cells' matrices
+    double cell_bytes(double w) const;  // of one product of all systems, w bytes a scalar
     bool spmv_shared = false;  // some group has two or more members
     int64_t xi_total = 0;      // complex entries of the member-interleaved copy (see SpmvGroup::xoff)
     Sched ilsched;             // blocks of the preconditioner's interleaved output, per group

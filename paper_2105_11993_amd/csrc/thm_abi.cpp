@@ -1188,7 +1188,7 @@ void thm_system_destroy(thm_system *sys) {
 // stream once its own is idle.  The kernels read and write the caller's vectors themselves;
 // vectors that overlap, or are not aligned for 16-byte accesses, go through the context's slots.
 // Against a copy in, a copy out and two stream joins, a product of 256^2 cells of degree 2 takes
-// 105 instead of 149 us (the kernel itself 87).
+// 51 instead of 95 us (its kernels 35).
 namespace {
 struct CallerVectors {
     Ctx &c;
@@ -1366,7 +1366,10 @@ thm_status thm_time_spmv(thm_system *sys, int32_t precision, int32_t reps, doubl
         *ms_out = ms / reps;
         const double v = f32 ? 4.0 : 8.0;
         const double nnz = (double)sys->K.col.size() + (double)sys->C.col.size();
-        if (bytes_out) *bytes_out = (v + 4.0) * nnz + 2.0 * 4.0 * (sys->n + 1) + 2.0 * 2.0 * sys->n * v;
+        if (bytes_out)
+            *bytes_out = (f32 ? c.lpr32 : c.lpr64) == THM_SPMV_CELLS
+                             ? c.cell_bytes(v)
+                             : (v + 4.0) * nnz + 2.0 * 4.0 * (sys->n + 1) + 2.0 * 2.0 * sys->n * v;
         stream_join(c.st, us);
     });
 }
@@ -1378,7 +1381,7 @@ thm_status thm_time_spmv_batch(thm_system *sys, int32_t precision, int32_t varia
         if (precision != THM_FP64 && precision != THM_FP32_IR) fail(THM_EINVAL, "unknown precision");
         if (!sys->ddm || !sys->ddm->inner) fail(THM_EINVAL, "no subdomain batch yet: run thm_ddm_solve first");
         static const int known[] = {21, 41, 81, 161, 321, 641, 24, 44, 84, 164, 324, THM_SPMV_SELL,
-                                    THM_SPMV_SELL_GROUP, THM_SPMV_SELL_GROUP_IL};
+                                    THM_SPMV_SELL_GROUP, THM_SPMV_SELL_GROUP_IL, THM_SPMV_CELLS};
         bool ok = variant == -1;
         for (int k : known) ok = ok || k == variant;
         if (!ok) fail(THM_EINVAL, "unknown SpMV variant");
@@ -1392,6 +1395,7 @@ thm_status thm_time_spmv_batch(thm_system *sys, int32_t precision, int32_t varia
         THM_HIP(hipEventCreate(&e0));
         THM_HIP(hipEventCreate(&e1));
         if (v == THM_SPMV_SELL_GROUP_IL) c.ensure_xi(f32);
+        if (v == THM_SPMV_CELLS && !c.ensure_cells()) fail(THM_EUNSUPPORTED, "K holds more than its cells' matrices");
         auto once = [&] {
             if (v == THM_SPMV_SELL_GROUP_IL) {
                 if (f32)
@@ -1424,7 +1428,7 @@ thm_status thm_time_spmv_batch(thm_system *sys, int32_t precision, int32_t varia
             }
             for (const thm_system *m : c.sys)  // per system: C, its row pointers, x read and y written
                 by += (w + 4.0) * (double)m->C.col.size() + 4.0 * (double)(m->n + 1) + 2.0 * 2.0 * m->n * w;
-            *bytes_out = by;
+            *bytes_out = v == THM_SPMV_CELLS ? c.cell_bytes(w) : by;
         }
         stream_join(c.st, us);
     });
@@ -1480,7 +1484,7 @@ thm_status thm_time_spmv_systems(int32_t nsys, thm_system *const *sys, int32_t p
                 if (v != THM_SPMV_SELL_GROUP) by += (w + 4.0) * (double)m->K.col.size() + 4.0 * (double)(m->n + 1);
                 by += (w + 4.0) * (double)m->C.col.size() + 4.0 * (double)(m->n + 1) + 2.0 * 2.0 * m->n * w;
             }
-            *bytes_out = by;
+            *bytes_out = v == THM_SPMV_CELLS ? c->cell_bytes(w) : by;
         }
         stream_join(c->st, us);
     });
@@ -1488,6 +1492,7 @@ thm_status thm_time_spmv_systems(int32_t nsys, thm_system *const *sys, int32_t p
 
 static_assert(THM_NOALLOC_SCRATCH_BYTES == thm::NOALLOC_SCRATCH_BYTES, "scratch size of the header and the library");
 static_assert(THM_SPMV_SELL_GROUP_IL == thm::SPMV_SELL_GROUP_IL, "interleaved grouped SpMV code");
+static_assert(THM_SPMV_CELLS == thm::SPMV_CELLS, "code of the product from the cells");
 static_assert(THM_SPMV_SELL == thm::SPMV_SELL && THM_SPMV_SELL_GROUP == thm::SPMV_SELL_GROUP,
               "SpMV variant codes of the header and the kernels differ");
 
@@ -1496,7 +1501,7 @@ thm_status thm_set_spmv_variant(thm_system *sys, int32_t precision, int32_t vari
         if (!sys) fail(THM_EINVAL, "bad arguments");
         if (precision != THM_FP64 && precision != THM_FP32_IR) fail(THM_EINVAL, "unknown precision");
         static const int known[] = {21, 41, 81, 161, 321, 641, 24, 44, 84, 164, 324, THM_SPMV_SELL,
-                                    THM_SPMV_SELL_GROUP, THM_SPMV_SELL_GROUP_IL};
+                                    THM_SPMV_SELL_GROUP, THM_SPMV_SELL_GROUP_IL, THM_SPMV_CELLS};
         bool ok = variant == -1;
         for (int k : known) ok = ok || k == variant;
         if (!ok) fail(THM_EINVAL, "unknown SpMV variant");
@@ -1506,7 +1511,11 @@ thm_status thm_set_spmv_variant(thm_system *sys, int32_t precision, int32_t vari
                 c.autotune();
                 return;
             }
-            if (variant != THM_SPMV_SELL_GROUP && variant != THM_SPMV_SELL_GROUP_IL) c.K.B.spmv_sched(variant, c.st);
+            if (variant == THM_SPMV_CELLS) {
+                if (!c.ensure_cells()) fail(THM_EUNSUPPORTED, "K holds more than its cells' matrices");
+            } else if (variant != THM_SPMV_SELL_GROUP && variant != THM_SPMV_SELL_GROUP_IL) {
+                c.K.B.spmv_sched(variant, c.st);
+            }
             if (precision == THM_FP64) c.lpr64 = variant;
             else c.lpr32 = variant;
         };
