@@ -194,6 +194,13 @@ void launch_norm_finish(const Batch &B, const double *part, const int32_t *mask,
                         double rtol, double *resid, int32_t *running, hipStream_t st);
 void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt, const double *part, double *out,
                         int ldo, int accumulate, hipStream_t st);
+void launch_solve_reset(const Batch &B, const int32_t *mask, int32_t *running, int32_t *iters, hipStream_t st);
+void launch_first_step(const Batch &B, const int32_t *running, int32_t *iters, const double *resid, double *resid0,
+                       hipStream_t st);
+// out (host memory as seen by kernels): per system n, a, b (a and b may be null)
+void launch_export(const Batch &B, const int32_t *n, const double *a, const double *b, double *out, hipStream_t st);
+// out: *jcnt, *est and the entries above the last of column *jcnt - 1 of H (one system)
+void launch_export_column(const int32_t *jcnt, const double *est, const double *H, int m, double *out, hipStream_t st);
 // Start of a cycle: tolerance read from rtol_d; resets *step_ctr (if non-null); writes each
 // system's running flag to hrun (host-visible, may be null).
 void launch_cycle_start(const Batch &B, const double *part, int32_t *running, int32_t *active, int32_t *jcnt,

@@ -986,6 +986,58 @@ __global__ void k_hsolve(int ns, const int32_t *__restrict__ running, const int3
     }
 }
 
+__global__ void k_solve_reset(int ns, const int32_t *__restrict__ mask, int32_t *__restrict__ running,
+                              int32_t *__restrict__ iters) {
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    if (s >= ns) return;
+    running[s] = mask[s];
+    iters[s] = 0;
+}
+// Counts the first step of the running systems and keeps the residuals before it.
+__global__ void k_first_step(int ns, const int32_t *__restrict__ running, int32_t *__restrict__ iters,
+                             const double *__restrict__ resid, double *__restrict__ resid0) {
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    if (s >= ns) return;
+    if (running[s]) iters[s] += 1;
+    resid0[s] = resid[s];
+}
+// Per system an integer and up to two numbers for the host, in its own memory.
+__global__ void k_export(int ns, const int32_t *__restrict__ n, const double *__restrict__ a,
+                         const double *__restrict__ b, double *__restrict__ out) {
+    const int s = blockIdx.x * 256 + threadIdx.x;
+    if (s >= ns) return;
+    out[3 * s] = n[s];
+    if (a) out[3 * s + 1] = a[s];
+    if (b) out[3 * s + 2] = b[s];
+}
+// Of one system: the column count, the residual estimate and the newest column of H.
+__global__ void k_export_column(const int32_t *__restrict__ jcnt, const double *__restrict__ est,
+                                const double *__restrict__ H, int m, double *__restrict__ out) {
+    const int j = *jcnt;
+    if (threadIdx.x == 0) {
+        out[0] = j;
+        out[1] = *est;
+    }
+    for (int i = threadIdx.x; i < 2 * j; i += 256) out[2 + i] = H[(int64_t)(j - 1) * 2 * (m + 1) + i];
+}
+void launch_solve_reset(const Batch &B, const int32_t *mask, int32_t *running, int32_t *iters, hipStream_t st) {
+    k_solve_reset<<<(B.ns + 255) / 256, 256, 0, st>>>(B.ns, mask, running, iters);
+    THM_HIP(hipGetLastError());
+}
+void launch_first_step(const Batch &B, const int32_t *running, int32_t *iters, const double *resid, double *resid0,
+                       hipStream_t st) {
+    k_first_step<<<(B.ns + 255) / 256, 256, 0, st>>>(B.ns, running, iters, resid, resid0);
+    THM_HIP(hipGetLastError());
+}
+void launch_export(const Batch &B, const int32_t *n, const double *a, const double *b, double *out, hipStream_t st) {
+    k_export<<<(B.ns + 255) / 256, 256, 0, st>>>(B.ns, n, a, b, out);
+    THM_HIP(hipGetLastError());
+}
+void launch_export_column(const int32_t *jcnt, const double *est, const double *H, int m, double *out, hipStream_t st) {
+    k_export_column<<<1, 256, 0, st>>>(jcnt, est, H, m, out);
+    THM_HIP(hipGetLastError());
+}
+
 // Zero the entries flagged in `dir` (Dirichlet rows) of a complex vector.
 template <class T>
 __global__ void k_zero_flagged(const int64_t *__restrict__ off, const int64_t *__restrict__ nvec,

@@ -46,9 +46,16 @@ void Krylov::init(const std::vector<int64_t> &n, int m_, hipStream_t st) {
     part.alloc((size_t)std::max(1, B.ds.nblocks) * B.maxcols);
     npart.alloc(std::max(1, B.vs.nblocks));
     for (DBuf<int32_t> *b : {&running, &active, &jcnt, &iters, &jcol, &actc}) b->alloc(ns);
+    resid0.alloc(ns);
     if (pinned) (void)hipHostFree(pinned);
+    if (host_out) (void)hipHostFree(host_out);
+    pinned = nullptr;
+    host_out = nullptr;
     THM_HIP(hipHostMalloc((void **)&pinned, sizeof(int32_t) * (NEV + 1) * std::max(ns, 1),
                           hipHostMallocMapped | hipHostMallocCoherent));
+    THM_HIP(hipHostMalloc((void **)&host_out, sizeof(double) * std::max(3 * ns, 2 * (m + 1) + 2),
+                          hipHostMallocMapped | hipHostMallocCoherent));
+    THM_HIP(hipHostGetDevicePointer((void **)&host_out_dev, host_out, 0));
     THM_HIP(hipHostGetDevicePointer((void **)&pinned_dev, pinned, 0));
     pinned_run = pinned + (size_t)NEV * std::max(ns, 1);
     pinned_run_dev = pinned_dev + (size_t)NEV * std::max(ns, 1);
@@ -105,6 +112,7 @@ Krylov::~Krylov() {
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
     if (pinned) (void)hipHostFree(pinned);
+    if (host_out) (void)hipHostFree(host_out);
 }
 
 // ------------------------------------------------------------------ GMRES
@@ -186,6 +194,65 @@ static void cycle_close(Krylov &K, const KOps<T> &ops, T *x, hipStream_t st) {
     launch_axpy<T, T>(B, K.running.p, nullptr, z, x, st);
 }
 
+// First step of an FP64 solve with the complete inverse: x += P^{-1} (b - A x), the norms and flags of a
+// cycle's start before and after it.  P^{-1} is the inverse to rounding, so this is a solve's only
+// step but for the tightest tolerances; an Arnoldi step adds its products, basis and projections, the
+// close of the cycle and a chunk that only finds the systems converged.  256^2 cells of degree 2 in
+// 4x4 subdomains, interface GMRES: 325 -> 230 ms, 16^3 cells in 2x2x2: 268 -> 203 ms (the fewer waits of
+// the outer loop included).
+static void first_step(Krylov &K, const KOps<double> &ops, const GmresParams &p, const double *b, double *x,
+                       const int32_t *mask_in, hipStream_t st) {
+    Batch &B = K.B;
+    launch_norm2<double>(B, mask_in, b, K.npart.p, st);
+    launch_norm_finish(B, K.npart.p, mask_in, K.bnorm.p, nullptr, 0.0, nullptr, nullptr, st);
+    launch_solve_reset(B, mask_in, K.running.p, K.iters.p, st);
+    if (!p.x_zero) {
+        ops.apply(x, K.w64.p, b, K.running.p);
+        launch_norm2<double>(B, K.running.p, K.w64.p, K.npart.p, st);
+    }
+    launch_cycle_start(B, K.npart.p, K.running.p, K.active.p, K.jcnt.p, K.bnorm.p, K.rtol_d.p, K.g.p, K.m, K.beta.p,
+                       K.resid.p, K.iters.p, p.max_iter, K.step_ctr.p, K.pinned_run_dev, st);
+    ops.prec(p.x_zero ? b : K.w64.p, K.z64.p, K.running.p);
+    launch_axpy<double, double>(B, K.running.p, nullptr, K.z64.p, x, st);
+    launch_first_step(B, K.running.p, K.iters.p, K.resid.p, K.resid0.p, st);
+    cycle_open<double>(K, ops, p, b, x, st);
+}
+
+// Systems whose residual the first step did not reduce start over from their initial guess.
+static void first_step_check(Krylov &K, const KOps<double> &ops, const GmresParams &p, const double *b, double *x,
+                             hipStream_t st) {
+    const int ns = K.B.ns;
+    std::vector<double> r0(ns), r1(ns);
+    THM_HIP(hipMemcpy(r0.data(), K.resid0.p, sizeof(double) * ns, hipMemcpyDeviceToHost));
+    THM_HIP(hipMemcpy(r1.data(), K.resid.p, sizeof(double) * ns, hipMemcpyDeviceToHost));
+    std::vector<int32_t> run(ns), undo(ns);
+    THM_HIP(hipMemcpy(run.data(), K.running.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost));
+    bool any = false;
+    for (int i = 0; i < ns; ++i) {
+        // a residual that is not finite has ended the system's run
+        undo[i] = (run[i] || !std::isfinite(r1[i])) && !(r1[i] < r0[i]);
+        run[i] = run[i] || undo[i];
+        any = any || undo[i];
+    }
+    if (!any) return;
+    for (int i = 0; i < ns; ++i) {
+        if (!undo[i]) continue;
+        const int64_t o = K.B.h_off[i], n = K.B.h_len[i];
+        if (p.x_zero) THM_HIP(hipMemsetAsync(x + o, 0, sizeof(double) * n, st));
+    }
+    THM_HIP(hipMemcpy(K.running.p, run.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice));
+    if (!p.x_zero) {
+        DBuf<int32_t> mask;
+        DBuf<double> neg;
+        mask.upload(undo, st);
+        neg.upload(std::vector<double>(ns, -1.0), st);
+        launch_axpy<double, double>(K.B, mask.p, neg.p, K.z64.p, x, st);
+        THM_HIP(hipStreamSynchronize(st));
+    }
+    cycle_open<double>(K, ops, p, b, x, st);
+    THM_HIP(hipStreamSynchronize(st));
+}
+
 // Arnoldi steps per chunk graph: GRAPH_SPC, or one step where a solve takes only a step or
 // two (the complete inverse), so that few steps run past convergence.
 template <class T>
@@ -194,15 +261,16 @@ static int chunk_steps(const KOps<T> &ops) {
 }
 
 // Captured once per (precision, operator, options, kind, vectors) and replayed: kind 0 is a
-// chunk of chunk_steps() Arnoldi steps, kind 1 closes a cycle and opens the next (b and x are
-// part of the key, their addresses being baked into the graph).
+// chunk of chunk_steps() Arnoldi steps, kind 1 closes a cycle and opens the next, kind 2 is the
+// first step (b, x and the mask are part of the key, their addresses being baked into the graph).
 template <class T>
 static hipGraphExec_t cycle_graph(Krylov &K, const KOps<T> &ops, const GmresParams &p, int kind, const T *b, T *x,
-                                  hipStream_t st) {
+                                  hipStream_t st, const int32_t *mask = nullptr) {
     const int key = TypeKey<T>::v * 2 + (ops.csign < 0 ? 1 : 0) + (ops.pkind >= 2 ? 4 : 0);
     Krylov::GraphSlot &s = K.slots[key][kind];
     if (s.exec && s.owner == ops.owner && s.orth == p.orth && s.max_iter == p.max_iter && s.cplx == p.cplx &&
-        s.pkind == ops.pkind && (kind == 0 || (s.b == (const void *)b && s.x == (const void *)x)))
+        s.pkind == ops.pkind && (kind == 0 || (s.b == (const void *)b && s.x == (const void *)x)) &&
+        (kind != 2 || (s.mask == mask && s.x_zero == p.x_zero)))
         return s.exec;
     const int spc = chunk_steps(ops);
     if (s.exec) (void)hipGraphExecDestroy(s.exec);
@@ -212,6 +280,8 @@ static hipGraphExec_t cycle_graph(Krylov &K, const KOps<T> &ops, const GmresPara
     try {
         if (kind == 0) {
             for (int i = 0; i < spc; ++i) arnoldi_step<T>(K, ops, p, spc, st);
+        } else if (kind == 2) {
+            if constexpr (std::is_same_v<T, double>) first_step(K, ops, p, b, x, mask, st);
         } else {
             cycle_close<T>(K, ops, x, st);
             cycle_open<T>(K, ops, p, b, x, st);
@@ -234,6 +304,8 @@ static hipGraphExec_t cycle_graph(Krylov &K, const KOps<T> &ops, const GmresPara
     s.key_T = TypeKey<T>::v;
     s.b = b;
     s.x = x;
+    s.mask = mask;
+    s.x_zero = p.x_zero;
     return s.exec;
 }
 
@@ -250,13 +322,15 @@ void gmres_run(Krylov &K, const KOps<T> &ops, const T *b, T *x, const int32_t *m
     const int ns = B.ns, m = K.m;
     K.ensure<T>(st);
     if (flexible(ops)) K.ensure_z<T>();
-    launch_norm2<T>(B, mask_in, b, K.npart.p, st);
-    launch_norm_finish(B, K.npart.p, mask_in, K.bnorm.p, nullptr, 0.0, nullptr, nullptr, st);
-    THM_HIP(hipMemcpyAsync(K.running.p, mask_in, sizeof(int32_t) * ns, hipMemcpyDeviceToDevice, st));
-    THM_HIP(hipMemsetAsync(K.iters.p, 0, sizeof(int32_t) * ns, st));
     K.rtol_h = p.rtol;
     THM_HIP(hipMemcpyAsync(K.rtol_d.p, &K.rtol_h, sizeof(double), hipMemcpyHostToDevice, st));
     const bool graph = p.use_graph && ops.graphable;
+    const bool first = graph && ops.pkind == 1 && std::is_same_v<T, double>;
+    if (!first) {
+        launch_norm2<T>(B, mask_in, b, K.npart.p, st);
+        launch_norm_finish(B, K.npart.p, mask_in, K.bnorm.p, nullptr, 0.0, nullptr, nullptr, st);
+        launch_solve_reset(B, mask_in, K.running.p, K.iters.p, st);
+    }
     if (!graph) {
         // host-driven: one launch sequence per Arnoldi step; the finish kernel of step j writes
         // the systems' flags to host slot j mod NEV, and the host checks the flags of step
@@ -265,8 +339,7 @@ void gmres_run(Krylov &K, const KOps<T> &ops, const T *b, T *x, const int32_t *m
             cycle_open<T>(K, ops, p, b, x, st);
             THM_HIP(hipStreamSynchronize(st));
             if (!any_set(K.pinned_run, ns)) break;
-            constexpr int LAG = 3;
-            static_assert(LAG + 1 < Krylov::NEV, "flag slots in flight must not wrap");
+            const int LAG = std::min(p.lag, Krylov::NEV - 2);  // the flag slots in flight must not wrap
             for (int step = 0; step < m; ++step) {
                 arnoldi_step<T>(K, ops, p, 1, st);
                 const int sl = step % Krylov::NEV;
@@ -285,10 +358,20 @@ void gmres_run(Krylov &K, const KOps<T> &ops, const T *b, T *x, const int32_t *m
     // find it inactive and do nothing) and one close-and-reopen graph.  The finish kernels of
     // chunk c leave the systems' flags in host slot c mod NEV; the host checks chunk c - 1
     // while chunk c runs, and the running flags once per cycle.
+    if constexpr (std::is_same_v<T, double>) {
+        if (first) {
+            THM_HIP(hipGraphLaunch(cycle_graph<T>(K, ops, p, 2, b, x, st, mask_in), st));
+            THM_HIP(hipStreamSynchronize(st));
+            if (!any_set(K.pinned_run, ns)) return;
+            first_step_check(K, ops, p, b, x, st);
+        }
+    }
     hipGraphExec_t chunk = cycle_graph<T>(K, ops, p, 0, b, x, st);
     hipGraphExec_t turn = cycle_graph<T>(K, ops, p, 1, b, x, st);
-    cycle_open<T>(K, ops, p, b, x, st);
-    THM_HIP(hipStreamSynchronize(st));
+    if (!first) {
+        cycle_open<T>(K, ops, p, b, x, st);
+        THM_HIP(hipStreamSynchronize(st));
+    }
     const int spc = chunk_steps(ops);
     const int nchunks = (m + spc - 1) / spc;
     static_assert(Krylov::NEV >= 4, "chunk flag slots in flight must not wrap");
@@ -1213,7 +1296,7 @@ KOps<double> Ctx::ops_mixed(float csign, int pk) {
 }
 
 void Ctx::solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::vector<int> &iters,
-                std::vector<int> &refines, std::vector<double> &resid) {
+                std::vector<int> &refines, std::vector<double> &resid, bool x_zero) {
     if (!mask) mask = mask_all.p;
     last_fb.assign(ns, 0);
     last_ir.assign(ns, 0);
@@ -1228,15 +1311,19 @@ void Ctx::solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::
     gp.orth = o.orth;
     gp.use_graph = o.use_graph != 0;
     gp.cplx = o.krylov == THM_KRYLOV_COMPLEX ? 1 : 0;
+    gp.x_zero = x_zero && o.precision == THM_FP64;
+    auto to_host = [&](const int32_t *n, const double *a, const double *b) {
+        launch_export(K.B, n, a, b, K.host_out_dev, st);
+        THM_HIP(hipStreamSynchronize(st));
+    };
+    const double *ho = K.host_out;
     const int pk = o.precond == THM_PREC_FULL ? 1 : 0;
     if (o.precision == THM_FP64) {
         gmres_run<double>(K, ops64(csign, true, pk), b64.p, x64.p, mask, gp, st);
-        THM_HIP(hipMemcpyAsync(hi.data(), K.iters.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipMemcpyAsync(hr.data(), K.resid.p, sizeof(double) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipStreamSynchronize(st));
+        to_host(K.iters.p, K.resid.p, nullptr);
         for (int i = 0; i < ns; ++i) {
-            iters[i] = hi[i];
-            resid[i] = hr[i];
+            iters[i] = (int)ho[3 * i];
+            resid[i] = ho[3 * i + 1];
         }
         return;
     }
@@ -1269,9 +1356,11 @@ void Ctx::solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::
     {
         // GMRES-IR from the start for every system (THM_IR_GMRES) or for the systems whose
         // classical step has already failed to contract in this context
-        std::vector<int32_t> hm(ns);
-        THM_HIP(hipMemcpyAsync(hm.data(), mask, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipStreamSynchronize(st));
+        std::vector<int32_t> hm(ns, 1);
+        if (mask != mask_all.p) {
+            THM_HIP(hipMemcpyAsync(hm.data(), mask, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, st));
+            THM_HIP(hipStreamSynchronize(st));
+        }
         bool any_sticky = false;
         for (int i = 0; i < ns; ++i) {
             fb[i] = hm[i] && (!classic || sticky[i]);
@@ -1284,10 +1373,12 @@ void Ctx::solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::
         A64.apply(x64.p, r64.p, b64.p, run_ir.p);
         launch_norm2<double>(K.B, run_ir.p, r64.p, K.npart.p, st);
         launch_norm_finish(K.B, K.npart.p, run_ir.p, rnorm.p, bnorm64.p, o.rtol, resid64.p, run_ir.p, st);
-        THM_HIP(hipMemcpyAsync(hi.data(), run_ir.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipMemcpyAsync(hr.data(), resid64.p, sizeof(double) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipMemcpyAsync(hrn.data(), rnorm.p, sizeof(double) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipStreamSynchronize(st));
+        to_host(run_ir.p, resid64.p, rnorm.p);
+        for (int i = 0; i < ns; ++i) {
+            hi[i] = (int32_t)ho[3 * i];
+            hr[i] = ho[3 * i + 1];
+            hrn[i] = ho[3 * i + 2];
+        }
         bool any_undo = false;
         for (int i = 0; i < ns; ++i) {
             undo[i] = stepped[i] && !(hr[i] <= 0.5 * prev[i]) && hr[i] > o.rtol;
@@ -1337,9 +1428,8 @@ void Ctx::solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::
         THM_HIP(hipMemsetAsync(x32.p, 0, sizeof(float) * x32.n, st));
         gmres_run<float>(K, A32, b32.p, x32.p, run_ir.p, ip, st);
         launch_axpy<double, float>(K.B, run_ir.p, rnorm.p, x32.p, x64.p, st);
-        THM_HIP(hipMemcpyAsync(hi.data(), K.iters.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost, st));
-        THM_HIP(hipStreamSynchronize(st));
-        for (int i = 0; i < ns; ++i) iters[i] += hi[i];
+        to_host(K.iters.p, nullptr, nullptr);
+        for (int i = 0; i < ns; ++i) iters[i] += (int)ho[3 * i];
     }
     if (classic) {
         THM_HIP(hipMemcpyAsync(hr.data(), resid64.p, sizeof(double) * ns, hipMemcpyDeviceToHost, st));

@@ -133,8 +133,13 @@ struct Krylov {
         float csign = 0.f;
         double rtol = -1.0;
         const void *owner = nullptr;
-        const void *b = nullptr, *x = nullptr;  // vectors baked into a cycle-turn graph
-    } slots[8][2];  // [precision, sign, preconditioner kind][chunk of steps, cycle turn]
+        const void *b = nullptr, *x = nullptr;  // vectors baked into a cycle-turn or first-step graph
+        const int32_t *mask = nullptr;          // and the first step's mask
+        bool x_zero = false;
+    } slots[8][3];  // [precision, sign, preconditioner kind][chunk of steps, cycle turn, first step]
+    // per system in coherent host memory: three numbers that a kernel leaves for the host
+    double *host_out = nullptr, *host_out_dev = nullptr;
+    DBuf<double> resid0;  // residuals before the first step
     void init(const std::vector<int64_t> &n, int m, hipStream_t st);
     template <class T> T *V();
     template <class T> T *w();
@@ -170,6 +175,8 @@ struct GmresParams {
     int orth = THM_ORTH_CGS;
     bool use_graph = true;
     int cplx = 1;  // complex-scalar Arnoldi (1) or real-scalar (0)
+    int lag = 3;   // host-driven steps in flight before their flags are looked at
+    bool x_zero = false;  // the initial guess is zero
 };
 
 template <class T>
@@ -263,9 +270,9 @@ struct Ctx {
     // inverse (pkind 1, transpose sign csign < 0)
     void prec32(int pkind, float csign, const float *x, float *y, const int32_t *mask);
     // Solve A x = b for the systems in mask (device, nullable = all); b64/x64 slots hold
-    // the right-hand sides and initial guesses (zero on Dirichlet rows).
+    // the right-hand sides and initial guesses (zero on Dirichlet rows; x_zero: all of them zero).
     void solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::vector<int> &iters,
-               std::vector<int> &refines, std::vector<double> &resid);
+               std::vector<int> &refines, std::vector<double> &resid, bool x_zero = false);
     void autotune();
     // Time `reps` applications of the cyclic-reduction phases (k_bcr_mfma launches only)
     // with HIP events on this context's stream; returns ms per application, and the

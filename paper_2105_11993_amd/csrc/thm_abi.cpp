@@ -656,7 +656,7 @@ struct DdmRun {
             }
             if (Gv) launch_ddm_rhs(D.ntouch, D.touch_sys.p, D.touch_dof.p, D.touch_ptr.p, D.touch_src.p, D.Bb.p, Gv, c.st);
             THM_HIP(hipMemsetAsync(c.x64.p, 0, sizeof(double) * c.x64.n, c.st));
-            c.solve(inner_o, 1.f, nullptr, it, rf, rs);
+            c.solve(inner_o, 1.f, nullptr, it, rf, rs, true);
             for (int v : it) maxit = std::max(maxit, v);
             for (int f : c.last_fb) fallbacks += f;
             for (int f : c.last_ir) gmres_ir += f;
@@ -681,7 +681,7 @@ struct DdmRun {
             for (int s = 0; s < ns; ++s) {
                 Ctx &c = *D.singles[s];
                 THM_HIP(hipMemsetAsync(c.x64.p, 0, sizeof(double) * c.x64.n, c.st));
-                c.solve(inner_o, 1.f, nullptr, it, rf, rs);
+                c.solve(inner_o, 1.f, nullptr, it, rf, rs, true);
                 maxit = std::max(maxit, it[0]);
                 fallbacks += c.last_fb[0];
                 gmres_ir += c.last_ir[0];
@@ -725,40 +725,67 @@ struct DdmRun {
 
 }  // namespace
 
-// Smallest singular value of the k x k upper triangular complex matrix R (column-major,
-// interleaved (re, im), leading dimension ld complex entries), by inverse iteration on R^H R:
-// x <- R^{-1} R^{-H} x, normalised; ||R^{-1} R^{-H} x|| -> 1 / sigma_min^2.
-static double sigma_min_upper(const std::vector<double> &R, int k, int ld) {
+// Upper triangular complex matrix, columns one after another, real and imaginary parts apart.
+struct UpperTriangle {
+    int k = 0;
+    std::vector<double> re, im;
+    void clear() {
+        k = 0;
+        re.clear();
+        im.clear();
+    }
+    void add(const double *col) {  // interleaved
+        for (int i = 0; i <= k; ++i) {
+            re.push_back(col[2 * i]);
+            im.push_back(col[2 * i + 1]);
+        }
+        ++k;
+    }
+    size_t column(int j) const { return (size_t)j * (j + 1) / 2; }
+};
+
+// Smallest singular value by inverse iteration on R^H R: x <- R^{-1} R^{-H} x, normalised;
+// ||R^{-1} R^{-H} x|| -> 1 / sigma_min^2.  Both substitutions run down columns.
+static double sigma_min_upper(const UpperTriangle &R) {
+    const int k = R.k;
     if (k <= 0) return 1.0;
-    auto re = [&](int i, int j) { return R[2 * ((int64_t)j * ld + i)]; };
-    auto im = [&](int i, int j) { return R[2 * ((int64_t)j * ld + i) + 1]; };
     std::vector<double> xr(k, 1.0 / std::sqrt((double)k)), xi(k, 0.0), yr(k), yi(k);
     double lam = 0.0;
     for (int it = 0; it < 12; ++it) {
         // R^H y = x (forward substitution): y_i = (x_i - sum_{l<i} conj(R_li) y_l) / conj(R_ii)
         for (int i = 0; i < k; ++i) {
-            double ar = xr[i], ai = xi[i];
-            for (int l = 0; l < i; ++l) {
-                const double rr = re(l, i), ri = -im(l, i);
-                ar -= rr * yr[l] - ri * yi[l];
-                ai -= rr * yi[l] + ri * yr[l];
+            const double *cr = R.re.data() + R.column(i), *ci = R.im.data() + R.column(i);
+            double sr[4] = {}, si[4] = {};  // sums of their own, so that they can run together
+            int l = 0;
+            for (; l + 4 <= i; l += 4)
+                for (int u = 0; u < 4; ++u) {
+                    sr[u] += cr[l + u] * yr[l + u] + ci[l + u] * yi[l + u];
+                    si[u] += cr[l + u] * yi[l + u] - ci[l + u] * yr[l + u];
+                }
+            for (; l < i; ++l) {
+                sr[0] += cr[l] * yr[l] + ci[l] * yi[l];
+                si[0] += cr[l] * yi[l] - ci[l] * yr[l];
             }
-            const double dr = re(i, i), di = -im(i, i), den = dr * dr + di * di;
+            const double ar = xr[i] - ((sr[0] + sr[1]) + (sr[2] + sr[3]));
+            const double ai = xi[i] - ((si[0] + si[1]) + (si[2] + si[3]));
+            const double dr = cr[i], di = -ci[i], den = dr * dr + di * di;
             if (!(den > 0.0)) return 0.0;
             yr[i] = (ar * dr + ai * di) / den;
             yi[i] = (ai * dr - ar * di) / den;
         }
         // R z = y (back substitution), z overwrites x
+        xr = yr;
+        xi = yi;
         for (int i = k - 1; i >= 0; --i) {
-            double ar = yr[i], ai = yi[i];
-            for (int l = i + 1; l < k; ++l) {
-                const double rr = re(i, l), ri = im(i, l);
-                ar -= rr * xr[l] - ri * xi[l];
-                ai -= rr * xi[l] + ri * xr[l];
+            const double *cr = R.re.data() + R.column(i), *ci = R.im.data() + R.column(i);
+            const double dr = cr[i], di = ci[i], den = dr * dr + di * di;
+            const double zr = (xr[i] * dr + xi[i] * di) / den, zi = (xi[i] * dr - xr[i] * di) / den;
+            xr[i] = zr;
+            xi[i] = zi;
+            for (int l = 0; l < i; ++l) {
+                xr[l] -= cr[l] * zr - ci[l] * zi;
+                xi[l] -= cr[l] * zi + ci[l] * zr;
             }
-            const double dr = re(i, i), di = im(i, i), den = dr * dr + di * di;
-            xr[i] = (ar * dr + ai * di) / den;
-            xi[i] = (ai * dr - ar * di) / den;
         }
         double nz = 0.0;
         for (int i = 0; i < k; ++i) nz += xr[i] * xr[i] + xi[i] * xi[i];
@@ -871,11 +898,9 @@ static void ddm_solve_impl(thm_system &G, const thm_solve_opts &o, double *E, th
         // matrix (the same as the Hessenberg's: the Givens rotations are unitary), kept as the
         // minimum over the run.  1e-2 caps it where FP32 inner solves stop gaining.
         const int ldr = D.outer->m + 1;
-        std::vector<double> Rh((size_t)2 * ldr * D.outer->m, 0.0);
+        UpperTriangle R;  // columns of the current cycle
         double smin = 1.0;
-        int rcols = 0;  // columns of the current cycle's R held in Rh
         ops.apply = [&](const double *x, double *y, const double *b, const int32_t *) {
-            THM_HIP(hipStreamSynchronize(st));
             ++napply;
             if (progress && napply % 10 == 0)
                 std::fprintf(stderr, "[thm] ddm outer apply %d, inner iterations so far %d, %.1f ms\n", napply,
@@ -883,17 +908,24 @@ static void ddm_solve_impl(thm_system &G, const thm_solve_opts &o, double *E, th
             run.inner_o.rtol = o.inner_rtol;
             if (o.relax_inner && !b) {
                 // explicit residuals b - A x at restarts stay tight
-                int32_t j = 0;
+                const double *ho = D.outer->host_out;
+                launch_export_column(D.outer->jcnt.p, D.outer->est.p, D.outer->H.p, D.outer->m,
+                                     D.outer->host_out_dev, st);
+                THM_HIP(hipStreamSynchronize(st));
+                const int j = (int)ho[0];
                 double r = 1.0;
-                THM_HIP(hipMemcpy(&j, D.outer->jcnt.p, sizeof(int32_t), hipMemcpyDeviceToHost));
                 if (j > 0) {
-                    THM_HIP(hipMemcpy(&r, D.outer->est.p, sizeof(double), hipMemcpyDeviceToHost));
+                    r = ho[1];
                     if (!(r > 0.0) || !(r < 1.0)) r = 1.0;
-                    if (j < rcols) rcols = 0;  // a new cycle
-                    THM_HIP(hipMemcpy(Rh.data() + (size_t)2 * ldr * rcols, D.outer->H.p + (size_t)2 * ldr * rcols,
-                                      sizeof(double) * 2 * ldr * (j - rcols), hipMemcpyDeviceToHost));
-                    rcols = j;
-                    smin = std::min(smin, sigma_min_upper(Rh, j, ldr));
+                    if (j < R.k) R.clear();  // a new cycle
+                    if (j == R.k + 1) {
+                        R.add(ho + 2);
+                    } else if (j > R.k) {
+                        std::vector<double> H((size_t)2 * ldr * j);
+                        THM_HIP(hipMemcpy(H.data(), D.outer->H.p, sizeof(double) * H.size(), hipMemcpyDeviceToHost));
+                        while (R.k < j) R.add(H.data() + (size_t)2 * ldr * R.k);
+                    }
+                    smin = std::min(smin, sigma_min_upper(R));
                 }
                 run.inner_o.rtol = std::max(o.inner_rtol, std::min(1e-2, smin * gp.rtol / r));
                 if (progress && napply % 10 == 0)
@@ -915,6 +947,7 @@ static void ddm_solve_impl(thm_system &G, const thm_solve_opts &o, double *E, th
         gp.rtol = o.rtol;
         gp.orth = o.orth;
         gp.use_graph = false;
+        gp.lag = 0;  // a step costs a solve of every subdomain
         gp.cplx = o.krylov == THM_KRYLOV_COMPLEX ? 1 : 0;
         int budget = o.max_outer;
         for (int attempt = 0; attempt < 4 && budget > 0; ++attempt) {
