@@ -243,9 +243,9 @@ void launch_nd_pack(const std::vector<NdFront> &h, const NdFront *d, hipStream_t
 // A block serves some row tiles of one node and direction, Y = M X with
 //   up:    M = G (c x b),                   X = r,               u = (children's u) + Y
 //   down:  M = [Dinv | -G^T] (b x (b + c)), X = [r; x_boundary], x = Y,
-// where r = rhs - (children's u on the own DoFs) is formed while X is staged in LDS (both
-// directions form it, so no phase writes what another block of it reads).  A block has four
-// waves; ks of them share one 16-row tile and split its columns, the others take the next
+// where r = rhs - (children's u on the own DoFs) is formed while X is read (both directions form
+// it, so no phase writes what another block of it reads).  A block has four or eight waves; ks of
+// them share one 16-row tile and split its columns, the others take the next
 // tiles.  A wave streams its tiles as contiguous 1 KiB runs (nd_slot), the first of them
 // requested before X is staged.  Vectors are position-major, the (re, im) pairs of a factor
 // group's members side by side.  The sums have a fixed order.
@@ -273,21 +273,21 @@ __device__ __forceinline__ int nd_block() {
 
 constexpr int ND_UNR = 4;  // tiles in flight per wave
 
-// Columns [k0, k0 + kn) of X for the block's members (LOG: log2 of the member slots), handed to
-// put(k, member, value).  KC: children lists per own row.
-template <class T, bool FWD, int LOG, int KC, class Put>
+// Columns [k0, k0 + kn) of X for the block's member, handed to put(k, value).  KC: children lists
+// per own row.
+template <class T, bool FWD, int KC, class Put>
 __device__ __forceinline__ void nd_stage_kc(const NdTask &tk, int k0, int kn, int K, const typename NdPair<T>::t *ws,
                                             const typename NdPair<T>::t *ys, const typename NdPair<T>::t *ub, Put put) {
     using T2 = typename NdPair<T>::t;
-    constexpr int U = LOG ? 4 : 2;
-    const int cs = tk.cs / 2, total = kn << LOG;
-    for (int s0 = threadIdx.x; s0 < total; s0 += 256 * U) {
+    constexpr int U = 2;
+    const int nt = blockDim.x;
+    for (int s0 = threadIdx.x; s0 < kn; s0 += nt * U) {
         int j[U], ch[U][KC ? KC : 1];
         bool own[U], ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int s = s0 + 256 * u, k = s >> LOG, m = s & ((1 << LOG) - 1), kk = k0 + k;
-            ok[u] = s < total && kk < K && m < tk.nm;
+            const int s = s0 + nt * u, kk = k0 + s;
+            ok[u] = s < kn && kk < K;
             own[u] = FWD || !ok[u] || kk < tk.b;
             j[u] = own[u] ? (ok[u] ? kk : 0) : tk.bpos[kk - tk.b];
 #pragma unroll
@@ -296,10 +296,9 @@ __device__ __forceinline__ void nd_stage_kc(const NdTask &tk, int k0, int kn, in
         T2 v[U], c[U][KC ? KC : 1];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int m = min((s0 + 256 * u) & ((1 << LOG) - 1), tk.nm - 1);
-            v[u] = (own[u] ? ws : ys)[(int64_t)j[u] * cs + m];
+            v[u] = (own[u] ? ws : ys)[j[u]];
 #pragma unroll
-            for (int x = 0; x < KC; ++x) c[u][x] = ub[(int64_t)max(ch[u][x], 0) * cs + m];
+            for (int x = 0; x < KC; ++x) c[u][x] = ub[max(ch[u][x], 0)];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -308,19 +307,18 @@ __device__ __forceinline__ void nd_stage_kc(const NdTask &tk, int k0, int kn, in
                 v[u].x -= ch[u][x] >= 0 ? c[u][x].x : (T)0;
                 v[u].y -= ch[u][x] >= 0 ? c[u][x].y : (T)0;
             }
-            const int s = s0 + 256 * u;
-            if (s < total) put(s >> LOG, s & ((1 << LOG) - 1), ok[u] ? v[u] : T2{0, 0});
+            if (s0 + nt * u < kn) put(s0 + nt * u, ok[u] ? v[u] : T2{0, 0});
         }
     }
 }
 
-template <class T, bool FWD, int LOG, class Put>
+template <class T, bool FWD, class Put>
 __device__ __forceinline__ void nd_stage(const NdTask &tk, int k0, int kn, int K, const typename NdPair<T>::t *ws,
                                          const typename NdPair<T>::t *ys, const typename NdPair<T>::t *ub, Put put) {
-    if (tk.kc == 0) nd_stage_kc<T, FWD, LOG, 0>(tk, k0, kn, K, ws, ys, ub, put);
-    else if (tk.kc == 1) nd_stage_kc<T, FWD, LOG, 1>(tk, k0, kn, K, ws, ys, ub, put);
-    else if (tk.kc == 2) nd_stage_kc<T, FWD, LOG, 2>(tk, k0, kn, K, ws, ys, ub, put);
-    else nd_stage_kc<T, FWD, LOG, 4>(tk, k0, kn, K, ws, ys, ub, put);
+    if (tk.kc == 0) nd_stage_kc<T, FWD, 0>(tk, k0, kn, K, ws, ys, ub, put);
+    else if (tk.kc == 1) nd_stage_kc<T, FWD, 1>(tk, k0, kn, K, ws, ys, ub, put);
+    else if (tk.kc == 2) nd_stage_kc<T, FWD, 2>(tk, k0, kn, K, ws, ys, ub, put);
+    else nd_stage_kc<T, FWD, 4>(tk, k0, kn, K, ws, ys, ub, put);
 }
 
 // The children's update of boundary row `row` of a node (member m).
@@ -342,25 +340,25 @@ __device__ __forceinline__ typename NdPair<T>::t nd_children(const NdTask &tk, i
 // One member (re, im): the 2-column product on the vector units (the matrix units would idle
 // in 14 of 16 columns and have the same FP64 rate).
 template <class T, bool FWD>
-__global__ void __launch_bounds__(256) k_nd_vec(const NdTask *__restrict__ tasks, const int32_t *__restrict__ memb,
+__global__ void __launch_bounds__(512) k_nd_vec(const NdTask *__restrict__ tasks, const int32_t *__restrict__ memb,
                                                 const int32_t *__restrict__ mask, const T *__restrict__ wsb,
                                                 T *__restrict__ ysb, T *__restrict__ ubb) {
     using T2 = typename NdPair<T>::t;
     using V = typename NdVec<T>::vec;
     constexpr int P = NdVec<T>::P;
     extern __shared__ __align__(32) char nd_lds[];
-    __shared__ T2 part_sum[4][16];
+    __shared__ T2 part_sum[8][16];
     T2 *xs = reinterpret_cast<T2 *>(nd_lds);
     const NdTask tk = tasks[nd_block()];
     if (mask && !mask[memb[tk.mbeg]]) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
     const int rows = FWD ? tk.c : tk.b, K = FWD ? tk.b : tk.b + tk.c;
     const int Kp = (K + ND_KS - 1) / ND_KS * ND_KS;
-    const int part = wave % tk.ks;
+    const int part = wave % tk.ks, nw = blockDim.x >> 6;
     const T2 *ws = reinterpret_cast<const T2 *>(wsb + tk.gbase) + tk.pos0;
     T2 *ys = reinterpret_cast<T2 *>(ysb + tk.gbase);
     T2 *ub = reinterpret_cast<T2 *>(ubb + tk.ubase);
-    for (int t0 = 0; t0 < tk.tiles; t0 += 4 / tk.ks) {
+    for (int t0 = 0; t0 < tk.tiles; t0 += nw / tk.ks) {
         const int rt = tk.rt0 + t0 + wave / tk.ks, row = rt * ND_RT + i16;
         const bool live = t0 + wave / tk.ks < tk.tiles && rt * ND_RT < rows;
         const bool out = live && part == 0 && g == 0 && row < rows;
@@ -380,7 +378,7 @@ __global__ void __launch_bounds__(256) k_nd_vec(const NdTask *__restrict__ tasks
             }
             if (t0 == 0 || Kp > ND_KC_VEC) {
                 if (t0 || k0) __syncthreads();
-                nd_stage<T, FWD, 0>(tk, k0, kn, K, ws, ys, ub, [&](int k, int, T2 v) { xs[k] = v; });
+                nd_stage<T, FWD>(tk, k0, kn, K, ws, ys, ub, [&](int k, T2 v) { xs[k] = v; });
                 __syncthreads();
             }
             if (FWD && k0 == 0 && out) add = nd_children<T>(tk, row, 0, ub);
@@ -443,72 +441,118 @@ template <> struct NdMma<double> {
     static __device__ __forceinline__ int row(int g, int v) { return g + 4 * v; }
 };
 
-// A member column is one row of the stage, padded by 16 bytes so that the 16 columns of a
-// 16-byte read fall into different banks.  Columns of absent members hold what was there:
-// they only reach outputs that are not stored.
+// Every wave reads its part of X straight into the operand registers: a position holds the members'
+// (re, im) pairs side by side, so 16 columns of 4 positions are four contiguous runs, and a wave is
+// the only reader of its columns in a block of ks = 4.  Staged in LDS instead, a block waited
+// for the lists and vectors of all its columns before its first product, in one to five rounds with
+// two barriers each, and held 64 KiB: 64^2 cells of degree 2, sixteen members, FP64, the phase
+// of 288 + 192 columns 98 -> 52 us; 32^2 cells, FP32, the root of 576 columns 17.5 -> 8.9 us.
+// Columns of absent members read the last member's: they only reach outputs that are not stored.
+template <class T, bool FWD, int KC, int NNT>
+__device__ __forceinline__ void nd_mfma_tile(const NdTask &tk, typename NdMma<T>::v4 (&acc)[NNT],
+                                             const typename NdVec<T>::vec *M, int pb, int pe, int K,
+                                             const T *__restrict__ ws, const T *__restrict__ ys,
+                                             const T *__restrict__ ub) {
+    using V = typename NdVec<T>::vec;
+    constexpr int P = NdVec<T>::P, U = 8 / P;  // 8 positions of a lane in flight
+    const int lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
+    const int b = tk.b;
+    const int64_t cs = tk.cs;
+    int col[NNT];
+#pragma unroll
+    for (int nt = 0; nt < NNT; ++nt) col[nt] = min(16 * nt + i16, 2 * tk.nm - 1);
+    for (int q = pb; q < pe; q += U) {
+        V a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = M[(int64_t)min(q + u, pe - 1) * 64];
+        T x[U][P][NNT];
+        const int k0 = 4 * P * q;
+        if (!FWD && k0 >= b && K > b) {  // boundary positions only: the same in the whole wave
+            int pos[U][P];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < P; ++t) pos[u][t] = tk.bpos[min(k0 + 4 * P * u + P * g + t, K - 1) - b];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < P; ++t)
+#pragma unroll
+                    for (int nt = 0; nt < NNT; ++nt) x[u][t][nt] = ys[pos[u][t] * cs + col[nt]];
+        } else {
+            int pos[U][P], ch[U][P][KC ? KC : 1];
+            bool own[U][P];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < P; ++t) {
+                    const int k = min(k0 + 4 * P * u + P * g + t, K - 1);
+                    own[u][t] = FWD || k < b;
+                    pos[u][t] = own[u][t] ? k : tk.bpos[k - b];
+#pragma unroll
+                    for (int c = 0; c < KC; ++c) ch[u][t][c] = own[u][t] ? tk.cidx[k * KC + c] : -1;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < P; ++t)
+#pragma unroll
+                    for (int nt = 0; nt < NNT; ++nt) {
+                        T v = (own[u][t] ? ws : ys)[pos[u][t] * cs + col[nt]];
+                        T w[KC ? KC : 1];
+#pragma unroll
+                        for (int c = 0; c < KC; ++c) w[c] = ub[max(ch[u][t][c], 0) * cs + col[nt]];
+#pragma unroll
+                        for (int c = 0; c < KC; ++c) v -= ch[u][t][c] >= 0 ? w[c] : (T)0;
+                        x[u][t][nt] = v;
+                    }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (q + u >= pe) break;
+#pragma unroll
+            for (int t = 0; t < P; ++t) {
+                const bool in = k0 + 4 * P * u + P * g + t < K;  // M is zero there, X need not be finite
+#pragma unroll
+                for (int nt = 0; nt < NNT; ++nt) acc[nt] = NdMma<T>::op(a[u][t], in ? x[u][t][nt] : (T)0, acc[nt]);
+            }
+        }
+    }
+}
+
 template <class T, bool FWD, int NNT>
-__device__ __forceinline__ void nd_mfma_tiles(const NdTask &tk, T *xs, const int32_t *__restrict__ memb,
+__device__ __forceinline__ void nd_mfma_tiles(const NdTask &tk, T *lds, const int32_t *__restrict__ memb,
                                               const int32_t *__restrict__ mask, const T *__restrict__ wsb,
                                               T *__restrict__ ysb, T *__restrict__ ubb) {
     using T2 = typename NdPair<T>::t;
     using V = typename NdVec<T>::vec;
     using V4 = typename NdMma<T>::v4;
-    constexpr int P = NdVec<T>::P, KC = nd_kc_mfma(sizeof(T), NNT), LOG = NNT == 1 ? 3 : 4;
+    constexpr int P = NdVec<T>::P;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i16 = lane & 15, g = lane >> 4;
     const int rows = FWD ? tk.c : tk.b, K = FWD ? tk.b : tk.b + tk.c;
-    const int Kp = (K + ND_KS - 1) / ND_KS * ND_KS, LD = min(Kp, KC) + P;
-    const int part = wave % tk.ks;
+    const int Kp = (K + ND_KS - 1) / ND_KS * ND_KS;
+    const int part = wave % tk.ks, nw = blockDim.x >> 6;
     const int64_t cs = tk.cs;
-    const T2 *ws = reinterpret_cast<const T2 *>(wsb + tk.gbase + tk.pos0 * cs) + tk.m0;
-    T2 *ys = reinterpret_cast<T2 *>(ysb + tk.gbase) + tk.m0;
-    T2 *ub = reinterpret_cast<T2 *>(ubb + tk.ubase) + tk.m0;
-    for (int t0 = 0; t0 < tk.tiles; t0 += 4 / tk.ks) {
+    const T *ws = wsb + tk.gbase + tk.pos0 * cs + 2 * tk.m0;
+    T *ys = ysb + tk.gbase + 2 * tk.m0;
+    T *ub = ubb + tk.ubase + 2 * tk.m0;
+    const int np = Kp / (4 * P), per = (np + tk.ks - 1) / tk.ks;
+    for (int t0 = 0; t0 < tk.tiles; t0 += nw / tk.ks) {
         const int rt = tk.rt0 + t0 + wave / tk.ks;
         const bool live = t0 + wave / tk.ks < tk.tiles && rt * ND_RT < rows;
         const V *M = reinterpret_cast<const V *>(static_cast<const T *>(tk.M) + (int64_t)(live ? rt : 0) * ND_RT * Kp) +
                      lane;
+        const int pb = part * per, pe = live ? min(np, pb + per) : pb;
         V4 acc[NNT];
 #pragma unroll
         for (int nt = 0; nt < NNT; ++nt) acc[nt] = V4{0, 0, 0, 0};
-        for (int k0 = 0; k0 < Kp; k0 += KC) {
-            const int kn = min(KC, Kp - k0);
-            const int np = kn / (4 * P), per = (np + tk.ks - 1) / tk.ks;
-            const int pb = part * per, pe = live ? min(np, pb + per) : pb;
-            const V *Mc = M + (int64_t)(k0 / (4 * P)) * 64;
-            V cur[ND_UNR];
-            if (pb < pe) {
-#pragma unroll
-                for (int u = 0; u < ND_UNR; ++u) cur[u] = Mc[(int64_t)min(pb + u, pe - 1) * 64];
-            }
-            if (t0 == 0 || Kp > KC) {
-                if (t0 || k0) __syncthreads();
-                nd_stage<T, FWD, LOG>(tk, k0, kn, K, ws, ys, ub, [&](int k, int m, T2 v) {
-                    xs[2 * m * LD + k] = v.x;
-                    xs[(2 * m + 1) * LD + k] = v.y;
-                });
-                __syncthreads();
-            }
-            for (int q = pb; q < pe; q += ND_UNR) {
-                V nxt[ND_UNR];
-#pragma unroll
-                for (int u = 0; u < ND_UNR; ++u) nxt[u] = Mc[(int64_t)min(q + ND_UNR + u, pe - 1) * 64];
-#pragma unroll
-                for (int u = 0; u < ND_UNR; ++u) {
-                    if (q + u >= pe) break;
-#pragma unroll
-                    for (int nt = 0; nt < NNT; ++nt) {
-                        const V x = *reinterpret_cast<const V *>(xs + (16 * nt + i16) * LD + 4 * P * (q + u) + P * g);
-#pragma unroll
-                        for (int t = 0; t < P; ++t) acc[nt] = NdMma<T>::op(cur[u][t], x[t], acc[nt]);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < ND_UNR; ++u) cur[u] = nxt[u];
-            }
-        }
-        // waves sharing a tile: partial tiles through LDS (behind the stage), summed by the first
+        if (tk.kc == 0) nd_mfma_tile<T, FWD, 0, NNT>(tk, acc, M, pb, pe, K, ws, ys, ub);
+        else if (tk.kc == 1) nd_mfma_tile<T, FWD, 1, NNT>(tk, acc, M, pb, pe, K, ws, ys, ub);
+        else if (tk.kc == 2) nd_mfma_tile<T, FWD, 2, NNT>(tk, acc, M, pb, pe, K, ws, ys, ub);
+        else nd_mfma_tile<T, FWD, 4, NNT>(tk, acc, M, pb, pe, K, ws, ys, ub);
+        // waves sharing a tile: partial tiles through LDS, summed by the first
         if (tk.ks > 1) {
-            V4 *red = reinterpret_cast<V4 *>(xs + nd_pad(16 * NNT * LD, 8));
+            V4 *red = reinterpret_cast<V4 *>(lds);
             if (t0) __syncthreads();
             if (part > 0)
 #pragma unroll
@@ -533,10 +577,10 @@ __device__ __forceinline__ void nd_mfma_tiles(const NdTask &tk, T *xs, const int
                 const int row = rt * ND_RT + NdMma<T>::row(g, v);
                 if (row >= rows) continue;
                 if (FWD) {
-                    const T2 a = nd_children<T>(tk, row, n / 2, ub);
-                    reinterpret_cast<T *>(ub)[(tk.uoff + row) * cs + n] = ((n & 1) ? a.y : a.x) + acc[nt][v];
+                    const T2 c = nd_children<T>(tk, row, n / 2, reinterpret_cast<const T2 *>(ub));
+                    ub[(tk.uoff + row) * cs + n] = ((n & 1) ? c.y : c.x) + acc[nt][v];
                 } else {
-                    reinterpret_cast<T *>(ys)[(tk.pos0 + row) * cs + n] = acc[nt][v];
+                    ys[(tk.pos0 + row) * cs + n] = acc[nt][v];
                 }
             }
         }
@@ -544,19 +588,19 @@ __device__ __forceinline__ void nd_mfma_tiles(const NdTask &tk, T *xs, const int
 }
 
 template <class T, bool FWD>
-__global__ void __launch_bounds__(256) k_nd_mfma(const NdTask *__restrict__ tasks, const int32_t *__restrict__ memb,
+__global__ void __launch_bounds__(512) k_nd_mfma(const NdTask *__restrict__ tasks, const int32_t *__restrict__ memb,
                                                  const int32_t *__restrict__ mask, const T *__restrict__ wsb,
                                                  T *__restrict__ ysb, T *__restrict__ ubb) {
     extern __shared__ __align__(32) char nd_lds[];
-    T *xs = reinterpret_cast<T *>(nd_lds);
+    T *lds = reinterpret_cast<T *>(nd_lds);
     const NdTask tk = tasks[nd_block()];
     if (mask) {
         const int lane = threadIdx.x & 63;
         const bool on = lane < tk.nm && mask[memb[tk.mbeg + tk.m0 + lane]];
         if (!__ballot(on)) return;  // the same in every wave
     }
-    if (tk.nm <= 8) nd_mfma_tiles<T, FWD, 1>(tk, xs, memb, mask, wsb, ysb, ubb);
-    else nd_mfma_tiles<T, FWD, 2>(tk, xs, memb, mask, wsb, ysb, ubb);
+    if (tk.nm <= 8) nd_mfma_tiles<T, FWD, 1>(tk, lds, memb, mask, wsb, ysb, ubb);
+    else nd_mfma_tiles<T, FWD, 2>(tk, lds, memb, mask, wsb, ysb, ubb);
 }
 
 template <class T, bool FWD>
@@ -566,12 +610,9 @@ static void launch_nd(const NdLaunch &L, const int32_t *memb, const int32_t *mas
     if (!L.nblocks) return;
     const size_t lds = L.lds;
     if (L.vec) {
-        k_nd_vec<T, FWD><<<L.nblocks, 256, lds, st>>>(t, memb, mask, ws, ys, ub);
+        k_nd_vec<T, FWD><<<L.nblocks, 64 * L.waves, lds, st>>>(t, memb, mask, ws, ys, ub);
     } else {
-        static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(k_nd_mfma<T, FWD>),
-                                                              hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-        (void)allowed;  // a refusal shows at the launch
-        k_nd_mfma<T, FWD><<<L.nblocks, 256, lds, st>>>(t, memb, mask, ws, ys, ub);
+        k_nd_mfma<T, FWD><<<L.nblocks, 64 * L.waves, lds, st>>>(t, memb, mask, ws, ys, ub);
     }
 }
 

@@ -122,11 +122,9 @@ struct NdTask {
     int16_t kc, ks;             // child lists per row; waves sharing a row tile
 };
 constexpr int ND_KC_VEC = 2048;  // columns staged at a time, one member
-// columns staged at a time by the matrix-core form with nnt tiles of 8 members (64 KiB of LDS)
-__host__ __device__ constexpr int nd_kc_mfma(int size, int nnt) { return 65536 / (16 * nnt * size); }
 struct NdLaunch {
     bool fwd = true, vec = true;    // vec: groups of one member
-    int nblocks = 0;
+    int nblocks = 0, waves = 4;     // waves of a block: 4 or 8
     size_t lds = 0;
     DBuf<NdTask> tasks;
 };

@@ -851,14 +851,17 @@ void Ctx::build_prec() {
 // Blocks of the nested-dissection groups, up the trees and down again: one launch per phase
 // and direction (two where a batch holds groups of one member and larger ones).  ks waves share
 // a 16-row tile so that a wave streams about 100 columns: narrow fronts do not pay for the
-// exchange of partial sums, wide ones keep enough requests in flight.  A phase of more than
-// 2048 blocks of one round each gives a block several rounds of tiles on the staged vector.
+// exchange of partial sums, wide ones keep enough requests in flight.  Fronts of more than 384
+// columns in a phase of at most one block per CU are shared by eight waves (the root of 64^2 cells of
+// degree 2, 1152 columns, sixteen members, FP64: 41 -> 25 us; narrower fronts: 8.9 -> 10.3 us).  A
+// phase of more than 2048 blocks of one round each gives a block several rounds of tiles.
 void Ctx::build_nd_tasks(bool f64, std::vector<NdLaunch> &out) {
     out.clear();
     size_t np = 0;
     for (const Group &G : groups)
         if (G.f->nd.plan) np = std::max(np, G.f->nd.plan->ph.size());
     auto add = [&](size_t q, bool fwd, bool vec) {
+        int nw = 4;  // waves of a block
         auto each = [&](auto visit) {
             for (const Group &G : groups) {
                 const NdForm &f = G.f->nd;
@@ -866,25 +869,37 @@ void Ctx::build_nd_tasks(bool f64, std::vector<NdLaunch> &out) {
                 for (size_t v = 0; v < f.plan->ph[q].node.size(); ++v) {
                     const NdNode &x = f.plan->ph[q].node[v];
                     const int rows = fwd ? x.c : x.b, k = fwd ? x.b : x.b + x.c;
-                    if (rows) visit(G, f, v, x, rows, k, k <= 96 ? 1 : k <= 192 ? 2 : 4);
+                    if (rows) visit(G, f, v, x, rows, k, k <= 96 ? 1 : k <= 192 ? 2 : k <= 384 || nw == 4 ? 4 : 8);
                 }
             }
         };
-        int64_t rounds = 0;  // block rounds of four waves
+        int64_t rounds = 0;  // block rounds
+        int widest = 0;
         double elems = 0.0, vecs = 0.0;
-        each([&](const Group &G, const NdForm &, size_t, const NdNode &, int rows, int k, int ks) {
-            const int nm = (int)G.mem.size(), tiles = (rows + ND_RT - 1) / ND_RT;
-            rounds += (int64_t)((tiles * ks + 3) / 4) * (vec ? 1 : (nm + 15) / 16);
-            elems += (double)rows * k;
-            vecs += nm * 2.0 * (k + rows);
-        });
+        auto count = [&] {
+            rounds = 0;
+            elems = vecs = 0.0;
+            each([&](const Group &G, const NdForm &, size_t, const NdNode &, int rows, int k, int ks) {
+                const int nm = (int)G.mem.size(), tiles = (rows + ND_RT - 1) / ND_RT;
+                rounds += (int64_t)((tiles * ks + nw - 1) / nw) * (vec ? 1 : (nm + 15) / 16);
+                elems += (double)rows * k;
+                vecs += nm * 2.0 * (k + rows);
+                widest = std::max(widest, k);
+            });
+        };
+        count();
         if (!rounds) return;
+        if (rounds <= 256 && widest > 384) {
+            nw = 8;
+            count();
+        }
         const int64_t per = std::max<int64_t>(1, rounds / 2048);
         const int64_t sz = f64 ? 8 : 4;
         std::vector<NdTask> tasks;
         NdLaunch L;
         L.fwd = fwd;
         L.vec = vec;
+        L.waves = nw;
         each([&](const Group &G, const NdForm &f, size_t v, const NdNode &x, int rows, int k, int ks) {
             const int nm = (int)G.mem.size(), tiles = (rows + ND_RT - 1) / ND_RT;
             const int64_t kp = nd_pad(k, ND_KS), off = fwd ? f.fo[q][v] : f.bo[q][v];
@@ -909,11 +924,9 @@ void Ctx::build_nd_tasks(bool f64, std::vector<NdLaunch> &out) {
                 if (vec) {
                     L.lds = std::max<size_t>(L.lds, 2 * sz * std::min<int64_t>(ND_KC_VEC, kp));
                 } else {
-                    const int64_t ld = std::min<int64_t>(nd_kc_mfma((int)sz, nnt), kp) + 16 / sz;
-                    L.lds = std::max<size_t>(L.lds,
-                                             sz * nd_pad(16 * nnt * ld, 8) + (ks > 1 ? sz * 4 * 64 * 4 * nnt : 0));
+                    L.lds = std::max<size_t>(L.lds, ks > 1 ? sz * 4 * 64 * nw * nnt : 0);
                 }
-                const int step = (int)per * (4 / ks);
+                const int step = (int)per * (nw / ks);
                 for (int r = 0; r < tiles; r += step) {
                     t.rt0 = r;
                     t.tiles = std::min(step, tiles - r);
