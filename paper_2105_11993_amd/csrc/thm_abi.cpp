@@ -729,27 +729,38 @@ struct DdmRun {
 struct UpperTriangle {
     int k = 0;
     std::vector<double> re, im;
-    void clear() {
-        k = 0;
-        re.clear();
-        im.clear();
-    }
+    std::vector<double> xr, xi;  // singular vector of the smallest singular value, so far
+    void clear() { *this = UpperTriangle(); }
     void add(const double *col) {  // interleaved
         for (int i = 0; i <= k; ++i) {
             re.push_back(col[2 * i]);
             im.push_back(col[2 * i + 1]);
         }
         ++k;
+        xr.push_back(1.0 / std::sqrt((double)k));
+        xi.push_back(0.0);
     }
     size_t column(int j) const { return (size_t)j * (j + 1) / 2; }
 };
 
 // Smallest singular value by inverse iteration on R^H R: x <- R^{-1} R^{-H} x, normalised;
-// ||R^{-1} R^{-H} x|| -> 1 / sigma_min^2.  Both substitutions run down columns.
-static double sigma_min_upper(const UpperTriangle &R) {
+// ||R^{-1} R^{-H} x|| -> 1 / sigma_min^2, from the vector of the columns before, until it changes by
+// less than 1e-3 (12 steps from a constant vector took 100 us per outer step at 85 columns on
+// average, an eighth of the step).  Both substitutions run down columns.
+static double sigma_min_upper(UpperTriangle &R) {
     const int k = R.k;
     if (k <= 0) return 1.0;
-    std::vector<double> xr(k, 1.0 / std::sqrt((double)k)), xi(k, 0.0), yr(k), yi(k);
+    std::vector<double> &xr = R.xr, &xi = R.xi, yr(k), yi(k);
+    {
+        double n = 0.0;
+        for (int i = 0; i < k; ++i) n += xr[i] * xr[i] + xi[i] * xi[i];
+        n = std::sqrt(n);
+        if (!(n > 0.0) || !std::isfinite(n)) return 0.0;
+        for (int i = 0; i < k; ++i) {
+            xr[i] /= n;
+            xi[i] /= n;
+        }
+    }
     double lam = 0.0;
     for (int it = 0; it < 12; ++it) {
         // R^H y = x (forward substitution): y_i = (x_i - sum_{l<i} conj(R_li) y_l) / conj(R_ii)
@@ -791,11 +802,13 @@ static double sigma_min_upper(const UpperTriangle &R) {
         for (int i = 0; i < k; ++i) nz += xr[i] * xr[i] + xi[i] * xi[i];
         nz = std::sqrt(nz);
         if (!(nz > 0.0) || !std::isfinite(nz)) return 0.0;
+        const bool settled = it > 0 && std::fabs(nz - lam) <= 1e-3 * nz;
         lam = nz;
         for (int i = 0; i < k; ++i) {
             xr[i] /= nz;
             xi[i] /= nz;
         }
+        if (settled) break;
     }
     return 1.0 / std::sqrt(lam);
 }
