@@ -24,7 +24,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PRECOND_REPS = 20      # timed applications of the preconditioner (roofline)
-PRECOND_LAUNCHES = 140  # their launches (7 per application on this workload)
+PRECOND_LAUNCHES = 100  # their launches (5 per application on this workload)
 WORKLOAD = ("2D unit square, 256x256 quads, Nedelec degree 2, w=50, kappa=1, mu=1, plane wave on x=0, "
             "impedance elsewhere, 4x4 subdomains, impedance-transmission DDM (interface GMRES), tol 1e-8")
 
@@ -163,7 +163,7 @@ def copy_bandwidth(torch, reps=10):
 
 
 def summarize_pmc(fetch_dir, write_dir, out_json):
-    """Per-launch HBM traffic of the cyclic-reduction kernel from two rocprofv3 --pmc runs
+    """Per-launch HBM traffic of the preconditioner's tree products from two rocprofv3 --pmc runs
     of this script (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch), each scaled by what the
     same counter reads for the reference copy.  Only the last PRECOND_REPS applications
     (the timing loop of thm_time_precond, every member active) are used."""
@@ -184,9 +184,9 @@ def summarize_pmc(fetch_dir, write_dir, out_json):
     for name, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = load(d, name)
         copy = [v for _, k, v in rows if "elementwise" in k and v > 0]
-        bcr = [v for _, k, v in rows if "k_bcr_mfma<float" in k]
+        bcr = [v for _, k, v in rows if "k_nd_mfma<float" in k]
         if not copy or not bcr:
-            sys.exit(f"{name}: no calibration or cyclic-reduction dispatches found under {d}")
+            sys.exit(f"{name}: no calibration or tree-product dispatches found under {d}")
         true_kib = COPY_MIB * 1024.0
         copy_kib = sorted(copy)[len(copy) // 2]
         factor = true_kib / copy_kib
@@ -195,7 +195,7 @@ def summarize_pmc(fetch_dir, write_dir, out_json):
                      "bcr_kib_per_launch": sum(tail) / len(tail), "bcr_dispatches": len(tail)}
     src = os.path.join(ROOT, "paper_2105_11993_amd", "csrc", "kernels_prec.hip")
     traffic = sum(v["bcr_kib_per_launch"] * 1024.0 * v["scale"] for v in res.values())
-    rec = {"kernel": "k_bcr_mfma<float,4>", "workload": WORKLOAD, "counters": res,
+    rec = {"kernel": "k_nd_mfma<float>", "workload": WORKLOAD, "counters": res,
            "hbm_bytes_per_launch": traffic,
            "kernels_prec_sha256": hashlib.sha256(open(src, "rb").read()).hexdigest()}
     with open(out_json, "w") as f:
@@ -207,7 +207,7 @@ def summarize_mfma(path, last=PRECOND_LAUNCHES):
     """Per kernel of a rocprofv3 counter run with MfmaUtil, MfmaFlopsF32 and MfmaFlopsF64: the
     dispatches' total duration (counter-run timestamps), MFMA flops (the MOPS counters x 512),
     achieved TFLOP/s and the duration-weighted MfmaUtil (MFMA busy cycles over GPU-active cycles
-    times SIMDs, in %).  For k_bcr_mfma<float> only the last `last` dispatches count (the timed
+    times SIMDs, in %).  For k_nd_mfma<float> only the last `last` dispatches count (the timed
     preconditioner applications at the end of the run, every member active)."""
     import collections
     import csv
@@ -221,7 +221,7 @@ def summarize_mfma(path, last=PRECOND_LAUNCHES):
         byk[k].append(v)
     out = {}
     for k, lst in byk.items():
-        sel = lst[-last:] if "k_bcr_mfma<float" in k else lst
+        sel = lst[-last:] if "k_nd_mfma<float" in k else lst
         t = sum(x["t"] for x in sel)
         fl = sum(x.get("MfmaFlopsF32", 0.0) + x.get("MfmaFlopsF64", 0.0) for x in sel)
         mu = sum(x.get("MfmaUtil", 0.0) * x["t"] for x in sel) / max(t, 1e-300)
@@ -231,7 +231,7 @@ def summarize_mfma(path, last=PRECOND_LAUNCHES):
 
 
 def measured_traffic(algorithmic_bytes_per_launch):
-    """HBM bytes per launch of the cyclic-reduction kernel from the committed counter runs
+    """HBM bytes per launch of the preconditioner's products from the committed counter runs
     (FETCH_SIZE + WRITE_SIZE, calibrated on a copy of known size), if they were taken on
     the kernel source as it is now; otherwise None."""
     import hashlib
@@ -526,8 +526,8 @@ def c3_leg(args, thm, torch, workloads, block_outer=0, mixed_full=None):
                             projected_s=per_solve * (best["outer_iters"] + 2))
         log(args, f"c3 {name} (capped): {capped[name]}")
     ms, by, nl = thm.thm_time_precond(S, thm.THM_FP64, reps=3)
-    roof = {"bound": "hbm", "kernel": "k_bcr_mfma<double,4> (batched FP64 MFMA products of the factorised K^{-1}, "
-                                      "block LU over 17 layers, 8 subdomains of 16^3; two per complete-inverse "
+    roof = {"bound": "hbm", "kernel": "k_nd_vec<double>, k_nd_mfma<double> (FP64 products of the factorised K^{-1}, nested "
+                                      "dissection of 8 subdomains of 16^3; two K^{-1} per complete-inverse "
                                       "application)",
             "achieved": by / ms / 1e6, "peak": 8000.0, "unit": "GB/s", "frac": by / ms / 1e6 / 8000.0,
             "launches_per_apply": nl, "avg_launch_us": ms / nl * 1e3, "bytes_per_apply": by}
@@ -800,7 +800,7 @@ def main():
                 ms, by = thm.thm_time_spmv_batch(S, prec, v, reps=50)
                 spmv_batch[f"{name}_{vname}"] = {"ms": ms, "bytes": by, "GBps": by / ms / 1e6}
         log(args, f"spmv batch: {spmv_batch}")
-    # dominant kernel of the timed solve: the cyclic-reduction multi-GEMV of the batched
+    # dominant kernel of the timed solve: the tree products of the batched
     # FP32 subdomain preconditioner (HIP events on the library stream, same launches as
     # inside the solve)
     ms, by, nl = thm.thm_time_precond(S, thm.THM_FP32_IR, reps=PRECOND_REPS)
@@ -809,7 +809,7 @@ def main():
     nsub = 1
     for v in geometry["subdomains"]:
         nsub *= v
-    roof = {"bound": "hbm", "kernel": f"k_bcr_mfma<float,4> (batched FP32 cyclic-reduction MFMA products, "
+    roof = {"bound": "hbm", "kernel": f"k_nd_mfma<float> (batched FP32 MFMA products of the nested dissection, "
                                       f"{nsub} subdomains)",
             "achieved": ach, "peak": peak, "unit": "GB/s", "frac": ach / peak,
             "traffic": measured_traffic(by / nl) if args.workload == "c2" and m == 256 else None,

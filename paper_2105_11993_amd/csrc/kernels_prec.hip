@@ -1,11 +1,12 @@
 // Block preconditioner diag(K, K)^{-1} of eq. (11) with an exact factorised K^{-1}:
 //  1. static condensation of the cell-interior DoFs (per-cell dense inverse),
-//  2. block cyclic reduction of the block-tridiagonal system on the skeleton
-//     (edge/face) DoFs, layered along the last axis: every level eliminates the
-//     odd-positioned blocks (explicit dense inverses) and couples the even ones.
-// Application to the two right-hand sides (real and imaginary halves) is one
-// batched MFMA launch per level and direction; systems whose matrices are identical
-// share one factor, and their right-hand sides become extra columns of one product.
+//  2. the condensed system on the skeleton (edge/face) DoFs by nested dissection (kernels_nd.hip),
+//     or, where THM_FACTOR_FORM selects it, in layers along the last axis: block cyclic
+//     reduction (every level eliminates the odd-positioned blocks and couples the even ones) or
+//     block LU.
+// This file holds the condensation, both ends of an application and the layered forms: one
+// batched MFMA launch per level and direction.  Systems whose matrices are identical share one
+// factor, and their right-hand sides become extra columns of one product.
 #include "nd.h"
 
 namespace thm {

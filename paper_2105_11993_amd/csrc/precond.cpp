@@ -1,7 +1,7 @@
 // Setup of the block preconditioner diag(K, K)^{-1} (eq. (11)) as an exact
-// factorised K^{-1}: static condensation of cell interiors, then block cyclic
-// reduction over the layers of skeleton DoFs (thin layers), or block LU (thick layers,
-// see plan_lu).  The paper approximates K^{-1} by an AMG with direct level transitions;
+// factorised K^{-1}: static condensation of cell interiors, then nested dissection of the
+// skeleton DoFs (setup_nd, nd.h).  THM_FACTOR_FORM selects one of the layered forms instead:
+// block cyclic reduction over the layers of skeleton DoFs, or block LU (plan_lu).  The paper approximates K^{-1} by an AMG with direct level transitions;
 // here the inverse is exact, so GMRES sees the preconditioned operator
 // I + [[0, -K^{-1}C], [K^{-1}C, 0]].
 //

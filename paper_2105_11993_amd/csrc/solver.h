@@ -11,7 +11,7 @@
 namespace thm {
 struct Ddm;
 
-// Exact factorised K^{-1} (condensation + block cyclic reduction), shareable by
+// Exact factorised K^{-1} (condensation, then nested dissection or a layered form), shareable by
 // systems with identical matrices.
 struct Factor {
     int nlayers = 0;
@@ -274,7 +274,7 @@ struct Ctx {
     void solve(const thm_solve_opts &o, float csign, const int32_t *mask, std::vector<int> &iters,
                std::vector<int> &refines, std::vector<double> &resid, bool x_zero = false);
     void autotune();
-    // Time `reps` applications of the cyclic-reduction phases (k_bcr_mfma launches only)
+    // Time `reps` applications of the factor's phases (tree or layered products only)
     // with HIP events on this context's stream; returns ms per application, and the
     // algorithmic bytes and number of launches per application.
     double time_bcr(int prec, int reps, double *bytes, int *launches);
