@@ -304,6 +304,9 @@ struct PrecPhase {
     int ntasks = 0;
 };
 
+struct CondQuad {
+    int32_t mem[4], nm;  // mem[j] for j >= nm repeats the last
+};
 struct PrecBatch {
     int ns = 0;
     DBuf<PrecDesc> d64, d32;
@@ -312,6 +315,8 @@ struct PrecBatch {
     Sched skel;                    // 256 skeleton entries per block
     Sched dofs;                    // 256 DoFs per block
     Sched cfr;                     // 256 (cell, skeleton local DoF) pairs per block
+    DBuf<CondQuad> quads;          // systems that share a factor, by four; empty: one system at a time
+    Sched qsched;                  // 256 DoFs per block of a quad
     DBuf<int64_t> toff;            // complex offset of each system's per-cell condensation terms
     int64_t Ttot = 0;              // complex entries of all condensation terms
     DBuf<int32_t> memb_ptr, memb;  // factor group -> member systems

@@ -729,6 +729,26 @@ void Ctx::build_prec() {
         }
         P.memb_ptr.upload(mp, st);
         P.memb.upload(mm, st);
+        // quads where they are at least half full, every factor is a tree and they make four blocks per CU
+        // (sixteen members of 64^2 cells of degree 2, FP64, 1160 blocks: 41 -> 25 us; of 32^2 cells, FP32, 296
+        // blocks: a solve 1.4% slower)
+        std::vector<CondQuad> quads;
+        std::vector<int64_t> units;
+        bool tree = true;
+        for (const Group &G : groups) {
+            tree = tree && G.f->nd.plan;
+            for (size_t m0 = 0; m0 < G.mem.size(); m0 += 4) {
+                CondQuad q{};
+                q.nm = (int32_t)std::min<size_t>(4, G.mem.size() - m0);
+                for (int j = 0; j < 4; ++j) q.mem[j] = G.mem[m0 + std::min(j, q.nm - 1)];
+                quads.push_back(q);
+                units.push_back(n[G.mem[m0]]);
+            }
+        }
+        if (tree && 2 * quads.size() <= (size_t)ns) {
+            P.qsched.build(units, 256, st);
+            if (P.qsched.nblocks >= 1024) P.quads.upload(quads, st);
+        }
     }
     // cyclic-reduction phases: forward levels, last blocks, backward levels
     int nlev = 0;
