@@ -514,7 +514,9 @@ static std::shared_ptr<NdPlan> nd_plan(thm_system &S, const std::vector<thm_syst
 // of K z = x in FP32 1.2e-3 with boxes of 8 x 8 cells, growth 15, and 4e-5 with boxes of 8 x 16;
 // in FP64 1e-11 and 1e-12).  So the growth of every halving level is found first, by a
 // factorisation with every level as a phase (narrow fronts: about a third of the time of the
-// other), and the phases start where it is small.
+// other), and the phases start where it is small.  A front of the probe may be singular where
+// the plan's are not, so the probe's pivots are reported to a word of its own; status also holds what the
+// condensation reported.
 static void setup_nd(const std::vector<thm_system *> &reps, const std::vector<std::shared_ptr<Factor>> &facs,
                      const std::vector<DBuf<double>> &kcond, const std::vector<thm_system *> &all, int32_t *status,
                      hipStream_t st) {
@@ -529,9 +531,9 @@ static void setup_nd(const std::vector<thm_system *> &reps, const std::vector<st
         jobs.push_back({&probe[g], reps[g], nullptr, nullptr, kcond[g].p});
         at.push_back(g);
     }
-    const std::vector<double> growth = factor_nd_all(jobs, status, st);
-    // a front of the probe may be singular where the plan's are not
-    THM_HIP(hipMemsetAsync(status, 0, sizeof(int32_t), st));
+    DBuf<int32_t> probe_status(1);
+    THM_HIP(hipMemsetAsync(probe_status.p, 0, sizeof(int32_t), st));
+    const std::vector<double> growth = factor_nd_all(jobs, probe_status.p, st);
     for (size_t t = 0; t < jobs.size(); ++t) {
         const NdPlan &p = *probe[at[t]].plan;
         for (size_t q = 0; q < p.ph.size(); ++q) {
