@@ -404,10 +404,11 @@ struct InvDesc {
     double *out;               // final inverse (n x n, leading dimension ldo)
     int32_t *piv;              // 2n: pivot rows (the column permutation at the end), row order
     int ldo;
+    int32_t *status;           // |= 1 for a zero or non-finite pivot
 };
 // Batched Gauss-Jordan inversion with partial pivoting in panels of 64 columns and rank-64
-// product updates (kernels_inv.hip); status |= 1 for a zero or non-finite pivot.
-void launch_invert_blocked(const std::vector<InvDesc> &d, int32_t *status, hipStream_t st);
+// product updates (kernels_inv.hip).
+void launch_invert_blocked(const std::vector<InvDesc> &d, hipStream_t st);
 // At (n x m, leading dimension ldt) = alpha * A^T, A (m x n, leading dimension lda)
 void launch_transpose(const double *A, int m, int n, int lda, double *At, int ldt, double alpha, hipStream_t st);
 void launch_compare(const void *a, const void *b, int64_t n8, int32_t *mismatch, hipStream_t st);

@@ -60,7 +60,7 @@ __device__ __forceinline__ void block_pivot(double &v, int &i, double *bv, int *
 // column is the first register of a row; the registers rotate by one a column, so that the loop
 // stays rolled.
 template <int R, int W>
-__global__ void __launch_bounds__(GJ_THREADS) k_bgj_strip(const InvDesc *__restrict__ ds, int c0, int32_t *status) {
+__global__ void __launch_bounds__(GJ_THREADS) k_bgj_strip(const InvDesc *__restrict__ ds, int c0) {
     __shared__ double bv[2][GJ_THREADS / 64], prow[2][W], crow[2][W];
     __shared__ int bi[2][GJ_THREADS / 64];
     const InvDesc d = ds[blockIdx.x];
@@ -154,11 +154,11 @@ __global__ void __launch_bounds__(GJ_THREADS) k_bgj_strip(const InvDesc *__restr
             }
             __builtin_amdgcn_wave_barrier();
         }
-    if (t == 0 && bad) atomicOr(status, 1);
+    if (t == 0 && bad) atomicOr(d.status, 1);
 }
 
 // A strip of one column in memory, for matrices of more rows than a block can hold.
-__global__ void __launch_bounds__(GJ_THREADS) k_bgj_column(const InvDesc *__restrict__ ds, int col, int32_t *status) {
+__global__ void __launch_bounds__(GJ_THREADS) k_bgj_column(const InvDesc *__restrict__ ds, int col) {
     __shared__ double bv[GJ_THREADS / 64], prow, crow;
     __shared__ int bi[GJ_THREADS / 64];
     const InvDesc d = ds[blockIdx.x];
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(GJ_THREADS) k_bgj_column(const InvDesc *__rest
         prow = d.A[(int64_t)p * n + col];
         crow = d.A[(int64_t)col * n + col];
         d.piv[col] = p;
-        if (!(v > 0.0) || !isfinite(v)) atomicOr(status, 1);
+        if (!(v > 0.0) || !isfinite(v)) atomicOr(d.status, 1);
     }
     __syncthreads();
     const double ipv = prow != 0.0 ? 1.0 / prow : 0.0;
@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(256) k_bgj_perm_apply(const InvDesc *__restric
     d.out[(int64_t)i * d.ldo + j] = d.A[(int64_t)i * n + d.piv[j]];
 }
 
-void launch_invert_blocked(const std::vector<InvDesc> &d, int32_t *status, hipStream_t st) {
+void launch_invert_blocked(const std::vector<InvDesc> &d, hipStream_t st) {
     if (d.empty()) return;
     const int nd = (int)d.size();
     int nmax = 0;
@@ -345,8 +345,8 @@ void launch_invert_blocked(const std::vector<InvDesc> &d, int32_t *status, hipSt
         for (int c0 = kb; c0 < kend; c0 += width) {
             auto strip = [&](auto rc) {
                 constexpr int R = decltype(rc)::value, W = gj_width(R);
-                if constexpr (W > 1) k_bgj_strip<R, W><<<nd, threads, 0, st>>>(dd.p, c0, status);
-                else k_bgj_column<<<nd, GJ_THREADS, 0, st>>>(dd.p, c0, status);
+                if constexpr (W > 1) k_bgj_strip<R, W><<<nd, threads, 0, st>>>(dd.p, c0);
+                else k_bgj_column<<<nd, GJ_THREADS, 0, st>>>(dd.p, c0);
                 k_bgj_swap<W><<<by_col, 256, 0, st>>>(dd.p, c0, kb, scr.p);
                 k_bgj_panel<W><<<by_row, 256, 0, st>>>(dd.p, c0, kb, scr.p);
             };

@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(256) k_nd_merge(const NdFront *__restrict__ fr
 // b <= ND_INV_MAX.  Rows stay in place: with p_k the pivot row of column k, the inverse is
 // Dinv[k][p_j] = A[p_k][j].  Bound by the LDS traffic of the rank-1 updates.
 constexpr int NDI_T = 512;
-__global__ void __launch_bounds__(NDI_T) k_nd_invert(const NdFront *__restrict__ fr, int32_t *status) {
+__global__ void __launch_bounds__(NDI_T) k_nd_invert(const NdFront *__restrict__ fr) {
     extern __shared__ __align__(16) double ndi_lds[];
     __shared__ int piv[ND_INV_MAX], used[ND_INV_MAX];
     __shared__ double prow[ND_INV_MAX], fcol[ND_INV_MAX];
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(NDI_T) k_nd_invert(const NdFront *__restrict__
             }
             if (lane == 0) {
                 if (!(best > 0.0) || !isfinite(best)) {
-                    atomicOr(status, 1);
+                    atomicOr(f.status, 1);
                     if (at >= n)  // a column of NaN: any unused row (the status reports it)
                         for (at = 0; used[at];) ++at;
                 }
@@ -177,11 +177,15 @@ __global__ void __launch_bounds__(256) k_nd_pack(const NdFront *__restrict__ fr,
 }
 
 constexpr double ND_GROWTH_MIN = ND_GROWTH[0];
-// Largest |G| beyond ND_GROWTH[0] (as bits: non-negative doubles order as integers).
+// Largest |G| beyond ND_GROWTH[0] (as bits: non-negative doubles order as integers); infinity where an
+// entry is not a number.
 __global__ void __launch_bounds__(256) k_nd_growth(const NdFront *__restrict__ fr) {
     const NdFront f = fr[blockIdx.x];
     double v = 0.0;
-    for (int64_t e = threadIdx.x; e < (int64_t)f.b * f.c; e += 256) v = fmax(v, fabs(f.G[e]));
+    for (int64_t e = threadIdx.x; e < (int64_t)f.b * f.c; e += 256) {
+        const double g = fabs(f.G[e]);
+        v = g <= HUGE_VAL ? fmax(v, g) : HUGE_VAL;
+    }
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     if ((threadIdx.x & 63) == 0 && v > ND_GROWTH_MIN) atomicMax(f.growth, __double_as_longlong(v));
 }
@@ -208,7 +212,7 @@ void launch_nd_merge(const std::vector<NdFront> &h, const NdFront *d, hipStream_
     THM_HIP(hipStreamSynchronize(st));  // the schedule ends here
 }
 
-void launch_nd_invert(const std::vector<NdFront> &h, const NdFront *d, int32_t *status, hipStream_t st) {
+void launch_nd_invert(const std::vector<NdFront> &h, const NdFront *d, hipStream_t st) {
     int n = 0;
     for (const NdFront &f : h)
         if (f.b <= ND_INV_MAX) n = std::max(n, f.b);
@@ -218,7 +222,7 @@ void launch_nd_invert(const std::vector<NdFront> &h, const NdFront *d, int32_t *
                                                           hipFuncAttributeMaxDynamicSharedMemorySize,
                                                           (int)(sizeof(double) * ND_INV_MAX * (ND_INV_MAX | 1)));
     (void)allowed;  // a refusal shows at the launch
-    k_nd_invert<<<(unsigned)h.size(), NDI_T, lds, st>>>(d, status);
+    k_nd_invert<<<(unsigned)h.size(), NDI_T, lds, st>>>(d);
     THM_HIP(hipGetLastError());
 }
 

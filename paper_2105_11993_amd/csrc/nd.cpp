@@ -69,8 +69,19 @@ constexpr double ND_LAUNCH_S = 6e-6, ND_BYTES_S = 5e12, ND_COL_S = 2e-6, ND_FLOP
 // or has to be finished in FP64.  (16^3 cells of degree 1 at w = 15, growth 20 to 190 on every
 // level: 8 levels started at 364 us an application, 5 in 486 us; a mixed solve 220 and 175 ms.)
 constexpr double ND_CLASS_COST[ND_CLASSES] = {0.0, 0.33, 0.6, 3.0};
+// The same for a level with a singular box: any tree without it is cheaper.
+constexpr double ND_BARRED_COST = 1e6;
 
 }  // namespace
+
+bool nd_avoidable(uint32_t barred, int levels) {
+    if (barred & 1u) return false;  // the root
+    for (int l = 0, run = 0; l < levels; ++l) {
+        run = (barred >> l) & 1u ? run + 1 : 0;
+        if (run >= ND_MERGE) return false;
+    }
+    return true;
+}
 
 void nd_plan_mesh(const Topo &t, NdPlan &P) {
     P.dim = t.dim;
@@ -166,7 +177,11 @@ void nd_plan_mesh(const Topo &t, NdPlan &P) {
                             (wide * ND_COL_S + flops / ND_FLOP_S) / ND_REUSE;
         }
     }
-    auto level_class = [&](int a) { return a > 0 && a < ND_LEVELS ? (int)((P.avoid >> (2 * a)) & 3u) : 0; };
+    auto is_barred = [&](int a) { return a > 0 && a < ND_LEVELS && ((P.barred >> a) & 1u); };
+    auto level_cost = [&](int a) {
+        if (is_barred(a)) return ND_BARRED_COST;
+        return ND_CLASS_COST[a > 0 && a < ND_LEVELS ? (P.avoid >> (2 * a)) & 3u : 0];
+    };
     std::vector<int> cut(D + 1, D);
     double least = 0.0;  // seconds of the cheapest plan, whatever its levels
     for (bool weigh : {false, true}) {
@@ -174,17 +189,22 @@ void nd_plan_mesh(const Topo &t, NdPlan &P) {
         best[D] = 0.0;
         for (int a = D - 1; a >= 0; --a)
             for (int z = a + 1; z <= std::min(D, a + ND_MERGE); ++z) {
-                const double s = seconds[a][z] + best[z] + (weigh ? ND_CLASS_COST[level_class(a)] * least : 0.0);
+                const double s = seconds[a][z] + best[z] + (weigh ? level_cost(a) * least : 0.0);
                 if (best[a] < 0.0 || s < best[a]) {
                     best[a] = s;
                     cut[a] = z;
                 }
             }
         least = best[0];
-        if (!P.avoid || P.avoid == ND_PROBE) break;
+        if ((!P.avoid && !P.barred) || P.avoid == ND_PROBE) break;
     }
     std::vector<int> from;  // first level of each phase, root first
-    for (int a = 0; a < D; a = P.avoid == ND_PROBE ? a + 1 : cut[a]) from.push_back(a);
+    if (P.avoid == ND_PROBE) {
+        for (int a = 0; a < D; ++a)
+            if (!is_barred(a)) from.push_back(a);
+    } else {
+        for (int a = 0; a < D; a = cut[a]) from.push_back(a);
+    }
     const int np = (int)from.size();
     std::reverse(from.begin(), from.end());  // leaves first
     std::vector<int> phase_of(D);

@@ -44,8 +44,9 @@ struct NdPlan {
     int dim = 0, p = 0, n[3] = {0, 0, 0};
     int64_t n_skel = 0, n_upd = 0;
     // class of every halving level as the start of a phase (two bits each); ND_PROBE: every
-    // level is a phase
+    // level is a phase, but for those in barred
     uint64_t avoid = 0;
+    uint32_t barred = 0;        // levels (bit each) where some box is singular
     int levels = 0;             // halving levels
     std::vector<int> from;      // first level of each phase
     std::vector<NdPhase> ph;    // leaves first
@@ -71,6 +72,8 @@ struct NdForm {
 };
 
 constexpr uint64_t ND_PROBE = ~uint64_t(0);
+// Some tree starts no phase at the levels in barred: they are no run of ND_MERGE or more.
+bool nd_avoidable(uint32_t barred, int levels);
 void nd_plan_mesh(const Topo &t, NdPlan &P);                     // host part
 void nd_build_plan(const Topo &t, NdPlan &P, hipStream_t st);    // with the device copies
 
@@ -94,7 +97,8 @@ struct NdFront {
     const int32_t *own;             // own DoFs
     const uint8_t *dir;             // Dirichlet flags (their rows become the identity)
     double *Dinv, *G;               // results: b x b, c x b
-    long long *growth;              // largest |G| of the phase beyond ND_GROWTH[0], as bits
+    long long *growth;              // largest |G| of the phase beyond ND_GROWTH[0], as bits (NaN as infinity)
+    int32_t *status;                // |= 1 for a zero or non-finite pivot
     double *m64;                    // apply matrices, FP64 and FP32
     float *m32;
     int64_t fo, bo;                 // element offsets of the two apply matrices
@@ -103,7 +107,7 @@ void launch_nd_leaf(const std::vector<NdFront> &h, const NdFront *d, hipStream_t
 void launch_nd_merge(const std::vector<NdFront> &h, const NdFront *d, hipStream_t st);
 // Dinv = F_oo^{-1} for the fronts with 0 < b <= ND_INV_MAX (one workgroup each, partial pivoting)
 constexpr int ND_INV_MAX = 128;
-void launch_nd_invert(const std::vector<NdFront> &h, const NdFront *d, int32_t *status, hipStream_t st);
+void launch_nd_invert(const std::vector<NdFront> &h, const NdFront *d, hipStream_t st);
 // A = F_oo as a contiguous matrix
 void launch_nd_own(const double *F, int n, int b, double *A, hipStream_t st);
 void launch_nd_growth(const std::vector<NdFront> &h, const NdFront *d, hipStream_t st);

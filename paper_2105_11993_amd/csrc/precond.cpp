@@ -331,7 +331,8 @@ struct NdJob {
 };
 
 // Numerical factorisation of a batch, one phase at a time over all of it: fronts, inverses of
-// the own blocks, G and the Schur complements, apply matrices.
+// the own blocks, G and the Schur complements, apply matrices.  Bad pivots are reported in
+// *status, those of probes in one word per job and phase.
 static void factor_nd(const NdJob *jobs, size_t nj, int32_t *status, long long *growth, hipStream_t st) {
     size_t np = 0;
     for (size_t t = 0; t < nj; ++t) np = std::max(np, jobs[t].form->plan->ph.size());
@@ -389,6 +390,7 @@ static void factor_nd(const NdJob *jobs, size_t nj, int32_t *status, long long *
                 r.m64 = job.m64;
                 r.m32 = job.m32;
                 r.growth = growth + ND_LEVELS * t + q;
+                r.status = job.m64 ? status : status + ND_LEVELS * t + q;
                 if (job.m64) {
                     r.fo = job.form->fo[q][v];
                     r.bo = job.form->bo[q][v];
@@ -404,7 +406,7 @@ static void factor_nd(const NdJob *jobs, size_t nj, int32_t *status, long long *
         dh.upload(h, st);
         if (q == 0) launch_nd_leaf(h, dh.p, st);
         else launch_nd_merge(h, dh.p, st);
-        launch_nd_invert(h, dh.p, status, st);
+        launch_nd_invert(h, dh.p, st);
         int64_t wide = 0, widep = 0;
         for (const NdFront &r : h)
             if (r.b > ND_INV_MAX) {
@@ -419,11 +421,11 @@ static void factor_nd(const NdJob *jobs, size_t nj, int32_t *status, long long *
             for (const NdFront &r : h) {
                 if (r.b <= ND_INV_MAX) continue;
                 launch_nd_own(r.F, r.b + r.c, r.b, work.p + o, st);
-                jobs.push_back({r.b, work.p + o, work.p + o + (int64_t)r.b * r.b, r.Dinv, piv.p + op, r.b});
+                jobs.push_back({r.b, work.p + o, work.p + o + (int64_t)r.b * r.b, r.Dinv, piv.p + op, r.b, r.status});
                 o += 2 * (int64_t)r.b * r.b;
                 op += 2 * r.b;
             }
-            launch_invert_blocked(jobs, status, st);
+            launch_invert_blocked(jobs, st);
         }
         std::vector<GemmDesc> ga, gb;
         for (const NdFront &r : h) {
@@ -446,12 +448,15 @@ static void factor_nd(const NdJob *jobs, size_t nj, int32_t *status, long long *
 
 // Factorise every job, in batches whose widest phase of fronts fits 8 GiB.  Returns the growth of
 // probes (jobs without matrices), ND_LEVELS entries each: the largest |G| per phase where it is
-// beyond ND_GROWTH[0], else 0.
+// beyond ND_GROWTH[0], else 0; infinity where a pivot was zero or not finite.
 static std::vector<double> factor_nd_all(std::vector<NdJob> &jobs, int32_t *status, hipStream_t st) {
     std::vector<double> h(ND_LEVELS * jobs.size(), 0.0);
     if (jobs.empty()) return h;
+    const bool probe = !jobs[0].m64;
     DBuf<long long> growth(h.size());
     THM_HIP(hipMemsetAsync(growth.p, 0, sizeof(long long) * growth.n, st));
+    DBuf<int32_t> bad(h.size());  // of probes
+    THM_HIP(hipMemsetAsync(bad.p, 0, sizeof(int32_t) * bad.n, st));
     for (size_t t0 = 0; t0 < jobs.size();) {
         size_t t1 = t0;
         int64_t words = 0;
@@ -466,11 +471,15 @@ static std::vector<double> factor_nd_all(std::vector<NdJob> &jobs, int32_t *stat
             words += most;
             ++t1;
         }
-        factor_nd(jobs.data() + t0, t1 - t0, status, growth.p + ND_LEVELS * t0, st);
+        factor_nd(jobs.data() + t0, t1 - t0, probe ? bad.p + ND_LEVELS * t0 : status, growth.p + ND_LEVELS * t0, st);
         t0 = t1;
     }
+    std::vector<int32_t> hb(h.size());
     THM_HIP(hipMemcpyAsync(h.data(), growth.p, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+    THM_HIP(hipMemcpyAsync(hb.data(), bad.p, sizeof(int32_t) * hb.size(), hipMemcpyDeviceToHost, st));
     THM_HIP(hipStreamSynchronize(st));
+    for (size_t i = 0; i < h.size(); ++i)
+        if (hb[i]) h[i] = HUGE_VAL;
     return h;
 }
 
@@ -491,19 +500,20 @@ static Form factor_form() {
     return Form::nd;
 }
 
-// The plan of a system's mesh that avoids the given levels, shared with the systems of the
+// The plan of a system's mesh that avoids the given levels (see NdPlan), shared with the systems of the
 // batch on the same mesh; a system keeps its plans (they depend on the mesh alone).
 static std::shared_ptr<NdPlan> nd_plan(thm_system &S, const std::vector<thm_system *> &others, uint64_t avoid,
-                                       hipStream_t st) {
+                                       uint32_t barred, hipStream_t st) {
     for (thm_system *o : others)
         for (const auto &p : o->nd)
-            if (p->avoid == avoid && p->matches(S.topo)) {
+            if (p->avoid == avoid && p->barred == barred && p->matches(S.topo)) {
                 if (o != &S) S.nd.push_back(p);
                 return p;
             }
     if (S.nd.size() >= 8) S.nd.erase(S.nd.begin() + 2);  // the default plan and the probe stay
     auto p = std::make_shared<NdPlan>();
     p->avoid = avoid;
+    p->barred = barred;
     nd_build_plan(S.topo, *p, st);
     S.nd.push_back(p);
     return p;
@@ -514,41 +524,60 @@ static std::shared_ptr<NdPlan> nd_plan(thm_system &S, const std::vector<thm_syst
 // of K z = x in FP32 1.2e-3 with boxes of 8 x 8 cells, growth 15, and 4e-5 with boxes of 8 x 16;
 // in FP64 1e-11 and 1e-12).  So the growth of every halving level is found first, by a
 // factorisation with every level as a phase (narrow fronts: about a third of the time of the
-// other), and the phases start where it is small.  A front of the probe may be singular where
-// the plan's are not, so the probe's pivots are reported to a word of its own; status also holds what the
-// condensation reported.
+// other), and the phases start where it is small.  A box can also be singular where larger and
+// smaller ones are not.  What the probe finds above the deepest level with such a box is of no use,
+// so that level is barred and the probe repeated without it, as long as some tree is left.  Its
+// pivots are reported apart from status, which also holds what the condensation reported.
 static void setup_nd(const std::vector<thm_system *> &reps, const std::vector<std::shared_ptr<Factor>> &facs,
                      const std::vector<DBuf<double>> &kcond, const std::vector<thm_system *> &all, int32_t *status,
                      hipStream_t st) {
     std::vector<uint64_t> avoid(facs.size(), 0);
+    std::vector<uint32_t> barred(facs.size(), 0);
     std::vector<NdForm> probe(facs.size());
     std::vector<NdJob> jobs;
     std::vector<size_t> at;
     for (size_t g = 0; g < facs.size(); ++g) {
-        facs[g]->nd.plan = nd_plan(*reps[g], all, 0, st);
-        if (facs[g]->nd.plan->ph.size() < 2) continue;  // a root alone has no G
-        probe[g].plan = nd_plan(*reps[g], all, ND_PROBE, st);
-        jobs.push_back({&probe[g], reps[g], nullptr, nullptr, kcond[g].p});
-        at.push_back(g);
+        facs[g]->nd.plan = nd_plan(*reps[g], all, 0, 0, st);
+        if (facs[g]->nd.plan->ph.size() >= 2) at.push_back(g);  // a root alone has no G
     }
-    DBuf<int32_t> probe_status(1);
-    THM_HIP(hipMemsetAsync(probe_status.p, 0, sizeof(int32_t), st));
-    const std::vector<double> growth = factor_nd_all(jobs, probe_status.p, st);
-    for (size_t t = 0; t < jobs.size(); ++t) {
-        const NdPlan &p = *probe[at[t]].plan;
-        for (size_t q = 0; q < p.ph.size(); ++q) {
-            const double v = growth[ND_LEVELS * t + q];
-            uint64_t cls = 0;
-            while (cls + 1 < ND_CLASSES && !(v <= ND_GROWTH[cls])) ++cls;
-            if (p.from[q] > 0 && p.from[q] < ND_LEVELS) avoid[at[t]] |= cls << (2 * p.from[q]);
-            if (std::getenv("THM_PROGRESS"))
-                std::fprintf(stderr, "[thm]   tree level %d: growth %.3g\n", p.from[q], v);
+    while (!at.empty()) {
+        jobs.clear();
+        for (size_t g : at) {
+            probe[g].plan = nd_plan(*reps[g], all, ND_PROBE, barred[g], st);
+            jobs.push_back({&probe[g], reps[g], nullptr, nullptr, kcond[g].p});
         }
+        const std::vector<double> growth = factor_nd_all(jobs, nullptr, st);
+        std::vector<size_t> again;
+        for (size_t t = 0; t < at.size(); ++t) {
+            const size_t g = at[t];
+            const NdPlan &p = *probe[g].plan;
+            const double *v = growth.data() + ND_LEVELS * t;
+            size_t deep = 0;  // phases run from the leaves up
+            while (deep < p.ph.size() && std::isfinite(v[deep])) ++deep;
+            if (deep < p.ph.size()) {
+                const uint32_t without = barred[g] | uint32_t(1) << p.from[deep];
+                if (std::getenv("THM_PROGRESS"))
+                    std::fprintf(stderr, "[thm]   tree level %d: singular\n", p.from[deep]);
+                if (nd_avoidable(without, p.levels)) {
+                    barred[g] = without;
+                    again.push_back(g);
+                    continue;
+                }
+            }
+            for (size_t q = 0; q < p.ph.size(); ++q) {
+                uint64_t cls = 0;
+                while (cls + 1 < ND_CLASSES && !(v[q] <= ND_GROWTH[cls])) ++cls;
+                if (p.from[q] > 0 && p.from[q] < ND_LEVELS) avoid[g] |= cls << (2 * p.from[q]);
+                if (std::getenv("THM_PROGRESS"))
+                    std::fprintf(stderr, "[thm]   tree level %d: growth %.3g\n", p.from[q], v[q]);
+            }
+        }
+        at = again;
     }
     jobs.clear();
     for (size_t g = 0; g < facs.size(); ++g) {
         Factor &f = *facs[g];
-        if (avoid[g]) f.nd.plan = nd_plan(*reps[g], all, avoid[g], st);
+        if (avoid[g] || barred[g]) f.nd.plan = nd_plan(*reps[g], all, avoid[g], barred[g], st);
         nd_offsets(f.nd);
         f.matp_elems = f.nd.elems;
         f.matp.alloc(std::max<int64_t>(f.matp_elems, 1));
@@ -676,11 +705,11 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
             const int n = ns[j];
             double *A = work.p + o, *Wb = work.p + o + (int64_t)n * n;
             THM_HIP(hipMemcpyAsync(A, jobs[j].first, sizeof(double) * n * n, hipMemcpyDeviceToDevice, st));
-            d.push_back({n, A, Wb, jobs[j].second.first, piv.p + op, jobs[j].second.second});
+            d.push_back({n, A, Wb, jobs[j].second.first, piv.p + op, jobs[j].second.second, status.p});
             o += 2 * (int64_t)n * n;
             op += 2 * n;
         }
-        launch_invert_blocked(d, status.p, st);
+        launch_invert_blocked(d, st);
     };
     const bool progress = std::getenv("THM_PROGRESS") != nullptr;
     if (progress)

@@ -1161,10 +1161,11 @@ void Ctx::build_full() {
                 launch_full_block(r, Sg.p + soff[s], full.cptr.p + goff[s], full.ccol.p, full.cval64.p, Bm.p + bo,
                                   st);
                 jobs.push_back(
-                    {2 * r, Bm.p + bo, Wk.p + bo, Inv.p + bo, piv.p + 4 * maxr_rep * (int64_t)(q - q0), 2 * r});
+                    {2 * r, Bm.p + bo, Wk.p + bo, Inv.p + bo, piv.p + 4 * maxr_rep * (int64_t)(q - q0), 2 * r,
+                     status.p});
                 bo += 4 * (int64_t)r * r;
             }
-            launch_invert_blocked(jobs, status.p, st);
+            launch_invert_blocked(jobs, st);
             bo = 0;
             for (size_t q = q0; q < q1; ++q) {
                 const int s = reps[q];
