@@ -196,7 +196,7 @@ void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt
                         int ldo, int accumulate, hipStream_t st);
 void launch_solve_reset(const Batch &B, const int32_t *mask, int32_t *running, int32_t *iters, hipStream_t st);
 void launch_first_step(const Batch &B, const int32_t *running, int32_t *iters, const double *resid, double *resid0,
-                       hipStream_t st);
+                       int32_t *stepped, hipStream_t st);
 // out (host memory as seen by kernels): per system n, a, b (a and b may be null)
 void launch_export(const Batch &B, const int32_t *n, const double *a, const double *b, double *out, hipStream_t st);
 // out: *jcnt, *est and the entries above the last of column *jcnt - 1 of H (one system)

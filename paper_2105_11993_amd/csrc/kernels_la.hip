@@ -993,12 +993,15 @@ __global__ void k_solve_reset(int ns, const int32_t *__restrict__ mask, int32_t 
     running[s] = mask[s];
     iters[s] = 0;
 }
-// Counts the first step of the running systems and keeps the residuals before it.
+// Counts the first step of the running systems, marks them and keeps their residuals before it.
 __global__ void k_first_step(int ns, const int32_t *__restrict__ running, int32_t *__restrict__ iters,
-                             const double *__restrict__ resid, double *__restrict__ resid0) {
+                             const double *__restrict__ resid, double *__restrict__ resid0,
+                             int32_t *__restrict__ stepped) {
     const int s = blockIdx.x * 256 + threadIdx.x;
     if (s >= ns) return;
-    if (running[s]) iters[s] += 1;
+    stepped[s] = running[s];
+    if (!running[s]) return;
+    iters[s] += 1;
     resid0[s] = resid[s];
 }
 // Per system an integer and up to two numbers for the host, in its own memory.
@@ -1025,8 +1028,8 @@ void launch_solve_reset(const Batch &B, const int32_t *mask, int32_t *running, i
     THM_HIP(hipGetLastError());
 }
 void launch_first_step(const Batch &B, const int32_t *running, int32_t *iters, const double *resid, double *resid0,
-                       hipStream_t st) {
-    k_first_step<<<(B.ns + 255) / 256, 256, 0, st>>>(B.ns, running, iters, resid, resid0);
+                       int32_t *stepped, hipStream_t st) {
+    k_first_step<<<(B.ns + 255) / 256, 256, 0, st>>>(B.ns, running, iters, resid, resid0, stepped);
     THM_HIP(hipGetLastError());
 }
 void launch_export(const Batch &B, const int32_t *n, const double *a, const double *b, double *out, hipStream_t st) {

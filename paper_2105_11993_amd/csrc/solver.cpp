@@ -47,6 +47,7 @@ void Krylov::init(const std::vector<int64_t> &n, int m_, hipStream_t st) {
     npart.alloc(std::max(1, B.vs.nblocks));
     for (DBuf<int32_t> *b : {&running, &active, &jcnt, &iters, &jcol, &actc}) b->alloc(ns);
     resid0.alloc(ns);
+    stepped.alloc(ns);
     if (pinned) (void)hipHostFree(pinned);
     if (host_out) (void)hipHostFree(host_out);
     pinned = nullptr;
@@ -214,7 +215,7 @@ static void first_step(Krylov &K, const KOps<double> &ops, const GmresParams &p,
                        K.resid.p, K.iters.p, p.max_iter, K.step_ctr.p, K.pinned_run_dev, st);
     ops.prec(p.x_zero ? b : K.w64.p, K.z64.p, K.running.p);
     launch_axpy<double, double>(B, K.running.p, nullptr, K.z64.p, x, st);
-    launch_first_step(B, K.running.p, K.iters.p, K.resid.p, K.resid0.p, st);
+    launch_first_step(B, K.running.p, K.iters.p, K.resid.p, K.resid0.p, K.stepped.p, st);
     cycle_open<double>(K, ops, p, b, x, st);
 }
 
@@ -227,10 +228,11 @@ static void first_step_check(Krylov &K, const KOps<double> &ops, const GmresPara
     THM_HIP(hipMemcpy(r1.data(), K.resid.p, sizeof(double) * ns, hipMemcpyDeviceToHost));
     std::vector<int32_t> run(ns), undo(ns);
     THM_HIP(hipMemcpy(run.data(), K.running.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost));
+    THM_HIP(hipMemcpy(undo.data(), K.stepped.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost));
     bool any = false;
     for (int i = 0; i < ns; ++i) {
         // a residual that is not finite has ended the system's run
-        undo[i] = (run[i] || !std::isfinite(r1[i])) && !(r1[i] < r0[i]);
+        undo[i] = undo[i] && (run[i] || !std::isfinite(r1[i])) && !(r1[i] < r0[i]);
         run[i] = run[i] || undo[i];
         any = any || undo[i];
     }

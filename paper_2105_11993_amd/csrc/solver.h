@@ -139,7 +139,8 @@ struct Krylov {
     } slots[8][3];  // [precision, sign, preconditioner kind][chunk of steps, cycle turn, first step]
     // per system in coherent host memory: three numbers that a kernel leaves for the host
     double *host_out = nullptr, *host_out_dev = nullptr;
-    DBuf<double> resid0;  // residuals before the first step
+    DBuf<double> resid0;   // residuals before the first step
+    DBuf<int32_t> stepped;  // systems that took it
     void init(const std::vector<int64_t> &n, int m, hipStream_t st);
     template <class T> T *V();
     template <class T> T *w();

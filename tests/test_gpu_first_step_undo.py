@@ -1,0 +1,45 @@
+"""First steps of FP64 solves with the complete inverse that do harm, and systems that take none."""
+import numpy as np
+import pytest
+
+from oracle import system
+from tests._gpu_helpers import dirichletized, problem, spec
+
+pytestmark = pytest.mark.gpu
+
+
+def box(dim, n, p, **kw):
+    return spec(dim, 1, p, 5.0, **dict(kw, n=tuple(n) + (1,) * (3 - dim)))
+
+
+@pytest.fixture(scope="module")
+def thm():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2105_11993_amd as t
+    return t
+
+
+def test_solved_system_beside_one_that_is_finished_in_fp64(thm):
+    """A system whose guess meets the tolerance takes no step in a mixed solve that ends with FP64 steps of
+    the other (no refinement, two steps of GMRES-based refinement allowed), for which the tolerance is
+    out of reach.  The solves before this one left a step and then residuals that are not numbers in the
+    workspace."""
+    import torch
+    print("case first step beside a solved system", flush=True)
+    ds = [box(2, (1, 1), 0), box(2, (13, 6), 2)]
+    Ss = [thm.thm_assemble(d) for d in ds]
+    Eo = [system.solve_lu(system.assemble(problem(d))) for d in ds]
+    opts = dict(precond=thm.THM_PREC_FULL, rtol=3e-16, restart=1, max_iter=2)
+    (E,), (st,) = thm.thm_gmres_solve(Ss[0], thm.default_opts(**dict(opts, max_iter=6)))
+    guess0 = E.clone()
+    for v in (1.0, float("nan")):
+        guess = [torch.full((S.n,), complex(v, 0.0), dtype=torch.complex128, device="cuda") for S in Ss]
+        thm.thm_gmres_solve(Ss, thm.default_opts(**opts), guess, allow_not_converged=True)
+    E0 = [guess0.clone(), torch.zeros(Ss[1].n, dtype=torch.complex128, device="cuda")]
+    Es, st = thm.thm_gmres_solve(Ss, thm.default_opts(precision=thm.THM_FP32_IR, max_refine=0, **opts), E0,
+                                 allow_not_converged=True)
+    print("  ", st, flush=True)
+    assert st[1]["fp64_fallback"] == 1 and st[0]["fp64_fallback"] == 0 and st[0]["status"] == 0
+    assert torch.equal(Es[0], guess0)
+    assert np.linalg.norm(Es[1].cpu().numpy() - Eo[1]) <= 1e-9 * np.linalg.norm(Eo[1])
