@@ -202,10 +202,12 @@ void launch_export(const Batch &B, const int32_t *n, const double *a, const doub
 // out: *jcnt, *est and the entries above the last of column *jcnt - 1 of H (one system)
 void launch_export_column(const int32_t *jcnt, const double *est, const double *H, int m, double *out, hipStream_t st);
 // Start of a cycle: tolerance read from rtol_d; resets *step_ctr (if non-null); writes each
-// system's running flag to hrun (host-visible, may be null).
+// system's running flag to hrun (host-visible, may be null).  With stepped (systems that took a first
+// step), only those whose residual is not below resid0 keep that mark, and their hrun is 2.
 void launch_cycle_start(const Batch &B, const double *part, int32_t *running, int32_t *active, int32_t *jcnt,
                         const double *bnorm, const double *rtol_d, double *g, int m, double *beta, double *resid,
-                        int32_t *iters, int max_iter, int32_t *step_ctr, int32_t *hrun, hipStream_t st);
+                        int32_t *iters, int max_iter, int32_t *step_ctr, int32_t *hrun, hipStream_t st,
+                        const double *resid0 = nullptr, int32_t *stepped = nullptr);
 // End of an Arnoldi step: V_{j+1} = cur = w / ||w||, column of H; the flags go to host slot
 // (step / spc) mod nslots.
 template <class T>

@@ -775,14 +775,16 @@ __global__ void __launch_bounds__(256) k_axpy(const int64_t *__restrict__ off, c
 // beta/bnorm <= rtol stop; otherwise g = (beta, 0, ...), jcnt = 0, active = 1.  The
 // tolerance is read from device memory (the launch may be replayed from a graph); the
 // step counter of the cycle is reset; each system's running flag is also written to
-// host-visible memory (hrun, may be null).
+// host-visible memory (hrun, may be null).  stepped (may be null) marks systems that took a first
+// step: only those whose residual is not below resid0 keep the mark, and 2 is written for them.
 __global__ void k_cycle_start(int ns, const int32_t *__restrict__ blkoff, const double *__restrict__ part,
                               int32_t *__restrict__ running, int32_t *__restrict__ active,
                               int32_t *__restrict__ jcnt, const double *__restrict__ bnorm,
                               const double *__restrict__ rtol_d, double *__restrict__ g, int m,
                               double *__restrict__ beta_out, double *__restrict__ resid_out,
                               int32_t *__restrict__ iters, int max_iter, int32_t *__restrict__ step_ctr,
-                              int32_t *__restrict__ hrun) {
+                              int32_t *__restrict__ hrun, const double *__restrict__ resid0,
+                              int32_t *__restrict__ stepped) {
     const int s = blockIdx.x;
     if (s >= ns) return;
     if (s == 0 && threadIdx.x == 0 && step_ctr) *step_ctr = 0;
@@ -802,14 +804,16 @@ __global__ void k_cycle_start(int ns, const int32_t *__restrict__ blkoff, const 
     resid_out[s] = rel;
     beta_out[s] = beta;
     jcnt[s] = 0;
+    const bool undo = stepped && stepped[s] && !(rel < resid0[s]);
+    if (stepped) stepped[s] = undo;
     if (!(rel > rtol) || iters[s] >= max_iter || !isfinite(rel)) {
         running[s] = 0;
         active[s] = 0;
-        if (hrun) hrun[s] = 0;
+        if (hrun) hrun[s] = undo ? 2 : 0;
         return;
     }
     active[s] = 1;
-    if (hrun) hrun[s] = 1;
+    if (hrun) hrun[s] = undo ? 2 : 1;
     gs[0] = beta;
 }
 
@@ -1132,9 +1136,10 @@ void launch_reduce_cols(const Batch &B, const int32_t *mask, const int32_t *jcnt
 }
 void launch_cycle_start(const Batch &B, const double *part, int32_t *running, int32_t *active, int32_t *jcnt,
                         const double *bnorm, const double *rtol_d, double *g, int m, double *beta, double *resid,
-                        int32_t *iters, int max_iter, int32_t *step_ctr, int32_t *hrun, hipStream_t st) {
+                        int32_t *iters, int max_iter, int32_t *step_ctr, int32_t *hrun, hipStream_t st,
+                        const double *resid0, int32_t *stepped) {
     k_cycle_start<<<B.ns, 256, 0, st>>>(B.ns, B.vs.blkoff.p, part, running, active, jcnt, bnorm, rtol_d,
-                                       g, m, beta, resid, iters, max_iter, step_ctr, hrun);
+                                       g, m, beta, resid, iters, max_iter, step_ctr, hrun, resid0, stepped);
     THM_HIP(hipGetLastError());
 }
 template <class T>

@@ -166,16 +166,18 @@ static void arnoldi_step(Krylov &K, const KOps<T> &ops, const GmresParams &p, in
 }
 
 // Start of a cycle: w = b - A x, beta = ||w||, stop test (running flags to host memory),
-// V_0 = cur = w / beta, step counter reset.
+// V_0 = cur = w / beta, step counter reset.  checked: systems whose first step did harm stay
+// marked in K.stepped and get 2 as their flag.
 template <class T>
 static void cycle_open(Krylov &K, const KOps<T> &ops, const GmresParams &p, const T *b, const T *x,
-                       hipStream_t st) {
+                       hipStream_t st, bool checked = false) {
     Batch &B = K.B;
     T *V = K.V<T>(), *w = K.w<T>(), *cur = K.cur<T>();
     ops.apply(x, w, b, K.running.p);
     launch_norm2<T>(B, K.running.p, w, K.npart.p, st);
     launch_cycle_start(B, K.npart.p, K.running.p, K.active.p, K.jcnt.p, K.bnorm.p, K.rtol_d.p, K.g.p, K.m,
-                       K.beta.p, K.resid.p, K.iters.p, p.max_iter, K.step_ctr.p, K.pinned_run_dev, st);
+                       K.beta.p, K.resid.p, K.iters.p, p.max_iter, K.step_ctr.p, K.pinned_run_dev, st, K.resid0.p,
+                       checked ? K.stepped.p : nullptr);
     launch_scale<T, T>(B, K.active.p, K.beta.p, 1, w, V, K.jcnt.p, B.Ltot, cur, st);
 }
 
@@ -216,41 +218,32 @@ static void first_step(Krylov &K, const KOps<double> &ops, const GmresParams &p,
     ops.prec(p.x_zero ? b : K.w64.p, K.z64.p, K.running.p);
     launch_axpy<double, double>(B, K.running.p, nullptr, K.z64.p, x, st);
     launch_first_step(B, K.running.p, K.iters.p, K.resid.p, K.resid0.p, K.stepped.p, st);
-    cycle_open<double>(K, ops, p, b, x, st);
+    cycle_open<double>(K, ops, p, b, x, st, true);
 }
 
-// Systems whose residual the first step did not reduce start over from their initial guess.
-static void first_step_check(Krylov &K, const KOps<double> &ops, const GmresParams &p, const double *b, double *x,
-                             hipStream_t st) {
+// Systems whose residual the first step did not reduce start over from their initial guess; at the
+// iteration limit they end with it.
+static void first_step_undo(Krylov &K, const KOps<double> &ops, const GmresParams &p, const double *b, double *x,
+                            hipStream_t st) {
     const int ns = K.B.ns;
-    std::vector<double> r0(ns), r1(ns);
-    THM_HIP(hipMemcpy(r0.data(), K.resid0.p, sizeof(double) * ns, hipMemcpyDeviceToHost));
-    THM_HIP(hipMemcpy(r1.data(), K.resid.p, sizeof(double) * ns, hipMemcpyDeviceToHost));
-    std::vector<int32_t> run(ns), undo(ns);
-    THM_HIP(hipMemcpy(run.data(), K.running.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost));
-    THM_HIP(hipMemcpy(undo.data(), K.stepped.p, sizeof(int32_t) * ns, hipMemcpyDeviceToHost));
+    std::vector<int32_t> run(ns);
     bool any = false;
     for (int i = 0; i < ns; ++i) {
-        // a residual that is not finite has ended the system's run
-        undo[i] = undo[i] && (run[i] || !std::isfinite(r1[i])) && !(r1[i] < r0[i]);
-        run[i] = run[i] || undo[i];
-        any = any || undo[i];
+        run[i] = K.pinned_run[i] != 0;
+        any = any || K.pinned_run[i] == 2;
     }
     if (!any) return;
-    for (int i = 0; i < ns; ++i) {
-        if (!undo[i]) continue;
-        const int64_t o = K.B.h_off[i], n = K.B.h_len[i];
-        if (p.x_zero) THM_HIP(hipMemsetAsync(x + o, 0, sizeof(double) * n, st));
-    }
-    THM_HIP(hipMemcpy(K.running.p, run.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice));
-    if (!p.x_zero) {
-        DBuf<int32_t> mask;
+    if (p.x_zero) {
+        for (int i = 0; i < ns; ++i)
+            if (K.pinned_run[i] == 2)
+                THM_HIP(hipMemsetAsync(x + K.B.h_off[i], 0, sizeof(double) * K.B.h_len[i], st));
+    } else {
         DBuf<double> neg;
-        mask.upload(undo, st);
         neg.upload(std::vector<double>(ns, -1.0), st);
-        launch_axpy<double, double>(K.B, mask.p, neg.p, K.z64.p, x, st);
+        launch_axpy<double, double>(K.B, K.stepped.p, neg.p, K.z64.p, x, st);
         THM_HIP(hipStreamSynchronize(st));
     }
+    THM_HIP(hipMemcpy(K.running.p, run.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice));
     cycle_open<double>(K, ops, p, b, x, st);
     THM_HIP(hipStreamSynchronize(st));
 }
@@ -364,8 +357,8 @@ void gmres_run(Krylov &K, const KOps<T> &ops, const T *b, T *x, const int32_t *m
         if (first) {
             THM_HIP(hipGraphLaunch(cycle_graph<T>(K, ops, p, 2, b, x, st, mask_in), st));
             THM_HIP(hipStreamSynchronize(st));
+            first_step_undo(K, ops, p, b, x, st);
             if (!any_set(K.pinned_run, ns)) return;
-            first_step_check(K, ops, p, b, x, st);
         }
     }
     hipGraphExec_t chunk = cycle_graph<T>(K, ops, p, 0, b, x, st);

@@ -123,7 +123,7 @@ struct Krylov {
     static constexpr int GRAPH_SPC = 8;
     int32_t *pinned = nullptr;  // NEV x ns host flags (coherent host memory, written by kernels)
     int32_t *pinned_dev = nullptr;  // the same memory as seen by kernels
-    int32_t *pinned_run = nullptr, *pinned_run_dev = nullptr;  // ns running flags of the current cycle
+    int32_t *pinned_run = nullptr, *pinned_run_dev = nullptr;  // ns running flags of the current cycle (2: the first step is to be undone)
     DBuf<int32_t> step_ctr;     // Arnoldi steps of the current cycle (selects the flag slot)
     hipEvent_t ev[NEV] = {};
     struct GraphSlot {
@@ -140,7 +140,7 @@ struct Krylov {
     // per system in coherent host memory: three numbers that a kernel leaves for the host
     double *host_out = nullptr, *host_out_dev = nullptr;
     DBuf<double> resid0;   // residuals before the first step
-    DBuf<int32_t> stepped;  // systems that took it
+    DBuf<int32_t> stepped;  // systems that took it; after its check those to be undone
     void init(const std::vector<int64_t> &n, int m, hipStream_t st);
     template <class T> T *V();
     template <class T> T *w();

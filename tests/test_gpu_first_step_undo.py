@@ -43,3 +43,24 @@ def test_solved_system_beside_one_that_is_finished_in_fp64(thm):
     assert st[1]["fp64_fallback"] == 1 and st[0]["fp64_fallback"] == 0 and st[0]["status"] == 0
     assert torch.equal(Es[0], guess0)
     assert np.linalg.norm(Es[1].cpu().numpy() - Eo[1]) <= 1e-9 * np.linalg.norm(Eo[1])
+
+
+def test_iteration_limit_of_one(thm):
+    """From a guess at rounding level the first step may end further off; the limit is reached after it, and
+    the better of the two vectors is returned."""
+    import torch
+    print("case first step, limit of one", flush=True)
+    rng = np.random.default_rng(21)
+    for k in range(24):
+        d = box(2, (4 + k % 5, 3 + k % 7), k % 3, mu=rng.uniform(1.0, 2.0, (4 + k % 5) * (3 + k % 7)))
+        S = thm.thm_assemble(d)
+
+        def run(E, max_iter):
+            o = thm.default_opts(precond=thm.THM_PREC_FULL, rtol=1e-30, max_iter=max_iter)
+            (E,), (st,) = thm.thm_gmres_solve(S, o, [E.clone()], allow_not_converged=True)
+            return E, st["rel_residual"], st["iters"]
+
+        E0, before, _ = run(torch.from_numpy(system.solve_lu(system.assemble(problem(d)))).cuda(), 6)
+        E0, before, n0 = run(E0, 0)
+        E1, after, n1 = run(E0, 1)
+        assert n0 == 0 and n1 <= 1 and after <= before, (k, before, after)
