@@ -215,6 +215,10 @@ static void first_step(Krylov &K, const KOps<double> &ops, const GmresParams &p,
     }
     launch_cycle_start(B, K.npart.p, K.running.p, K.active.p, K.jcnt.p, K.bnorm.p, K.rtol_d.p, K.g.p, K.m, K.beta.p,
                        K.resid.p, K.iters.p, p.max_iter, K.step_ctr.p, K.pinned_run_dev, st);
+    // the guess, for steps to be undone: x - z would not be it where z is large or not finite.  The second
+    // column of the basis is free until the first Arnoldi step.
+    if (!p.x_zero)
+        launch_scale<double, double>(B, K.running.p, nullptr, 0, x, K.V<double>() + B.Ltot, nullptr, 0, nullptr, st);
     ops.prec(p.x_zero ? b : K.w64.p, K.z64.p, K.running.p);
     launch_axpy<double, double>(B, K.running.p, nullptr, K.z64.p, x, st);
     launch_first_step(B, K.running.p, K.iters.p, K.resid.p, K.resid0.p, K.stepped.p, st);
@@ -238,10 +242,7 @@ static void first_step_undo(Krylov &K, const KOps<double> &ops, const GmresParam
             if (K.pinned_run[i] == 2)
                 THM_HIP(hipMemsetAsync(x + K.B.h_off[i], 0, sizeof(double) * K.B.h_len[i], st));
     } else {
-        DBuf<double> neg;
-        neg.upload(std::vector<double>(ns, -1.0), st);
-        launch_axpy<double, double>(K.B, K.stepped.p, neg.p, K.z64.p, x, st);
-        THM_HIP(hipStreamSynchronize(st));
+        launch_scale<double, double>(K.B, K.stepped.p, nullptr, 0, K.V<double>() + K.B.Ltot, x, nullptr, 0, nullptr, st);
     }
     THM_HIP(hipMemcpy(K.running.p, run.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice));
     cycle_open<double>(K, ops, p, b, x, st);

@@ -64,3 +64,22 @@ def test_iteration_limit_of_one(thm):
         E0, before, n0 = run(E0, 0)
         E1, after, n1 = run(E0, 1)
         assert n0 == 0 and n1 <= 1 and after <= before, (k, before, after)
+
+
+def test_step_that_is_not_finite(thm):
+    """Cells of side 2^500: K is of the order of 2^-1000 and C of 2^-500, so the first step from a guess of the
+    order of 2^1000 overflows, while the residual does not.  At the iteration limit the guess is returned."""
+    import torch
+    print("case first step, not finite", flush=True)
+    h = 2.0 ** 500
+    rng = np.random.default_rng(22)
+    d = spec(2, 1, 0, 1.0, n=(5, 4, 1), hi=(5 * h, 4 * h, 1.0), mu=rng.uniform(1.0, 2.0, 20),
+            eps=rng.uniform(0.1, 0.3, 20) * 2.0 ** -1000)
+    S = thm.thm_assemble(d)
+    free = thm.thm_export_rhs(S)[0] == 0
+    E0 = (rng.standard_normal(S.n) + 1j * rng.standard_normal(S.n)) * 2.0 ** 1000 * free
+    o = thm.default_opts(precond=thm.THM_PREC_FULL, rtol=1e-10, max_iter=1)
+    (E,), (st,) = thm.thm_gmres_solve(S, o, [torch.from_numpy(E0.copy()).cuda()], allow_not_converged=True)
+    print("  ", st, flush=True)
+    assert st["iters"] == 1 and np.isfinite(st["rel_residual"])
+    assert np.array_equal(E.cpu().numpy()[free], E0[free])
