@@ -189,6 +189,7 @@ struct Ctx {
     std::vector<thm_system *> sys;
     int ns = 0;
     hipStream_t st = nullptr;
+    bool own_stream = false;  // st was made for this context and goes with it
     Krylov K;
     PrecBatch P;
     DBuf<MatDesc> mat64, mat32;
@@ -256,6 +257,14 @@ struct Ctx {
     } full;
     void build_full();
 
+    Ctx() = default;
+    void make_stream() {
+        THM_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+        own_stream = true;
+    }
+    ~Ctx() {
+        if (own_stream && st) (void)hipStreamDestroy(st);
+    }
     // spmv_setup: form the SpMV groups and run the SpMV autotuner (not needed by a context
     // that only applies the preconditioner)
     void build(const std::vector<thm_system *> &s, int m, hipStream_t stream, bool spmv_setup = true);

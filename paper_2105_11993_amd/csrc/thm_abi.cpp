@@ -105,14 +105,8 @@ static Ctx &get_ctx(const std::vector<thm_system *> &sys, int m) {
     if (slot && slot->K.m != m) slot.reset();
     if (!slot) {
         auto c = std::make_unique<Ctx>();
-        hipStream_t st;
-        THM_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
-        try {
-            c->build(sys, m, st);
-        } catch (...) {
-            (void)hipStreamDestroy(st);
-            throw;
-        }
+        c->make_stream();
+        c->build(sys, m, c->st);
         slot = std::move(c);
     }
     return *slot;
@@ -823,9 +817,8 @@ static void ddm_prepare(thm_system &G, const thm_solve_opts &o, bool batched, hi
         if (!D.inner || D.inner->K.m != o.restart) {
             D.inner.reset();
             auto c = std::make_unique<Ctx>();
-            hipStream_t cs;
-            THM_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-            c->build(subs, o.restart, cs);
+            c->make_stream();
+            c->build(subs, o.restart, c->st);
             D.inner = std::move(c);
             std::vector<double *> xb, bb;
             for (int s = 0; s < D.nsub; ++s) {
@@ -841,9 +834,8 @@ static void ddm_prepare(thm_system &G, const thm_solve_opts &o, bool batched, hi
         std::vector<double *> xs, bs;
         for (int s = 0; s < D.nsub; ++s) {
             auto c = std::make_unique<Ctx>();
-            hipStream_t cs;
-            THM_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-            c->build({subs[s]}, o.restart, cs);
+            c->make_stream();
+            c->build({subs[s]}, o.restart, c->st);
             xs.push_back(c->x64.p);
             bs.push_back(c->b64.p);
             D.singles.push_back(std::move(c));
