@@ -500,21 +500,26 @@ static Form factor_form() {
     return Form::nd;
 }
 
-// The plan of a system's mesh that avoids the given levels (see NdPlan), shared with the systems of the
-// batch on the same mesh; a system keeps its plans (they depend on the mesh alone).
+// The plan of a system's mesh that avoids the given levels (see NdPlan): one that the system keeps
+// (plans depend on the mesh alone), one of another system of the batch on the same mesh, or a new one.
+constexpr size_t ND_KEPT = 8;  // plans a system keeps; the first two, the default and the probe, stay
 static std::shared_ptr<NdPlan> nd_plan(thm_system &S, const std::vector<thm_system *> &others, uint64_t avoid,
                                        uint32_t barred, hipStream_t st) {
-    for (thm_system *o : others)
-        for (const auto &p : o->nd)
-            if (p->avoid == avoid && p->barred == barred && p->matches(S.topo)) {
-                if (o != &S) S.nd.push_back(p);
-                return p;
-            }
-    if (S.nd.size() >= 8) S.nd.erase(S.nd.begin() + 2);  // the default plan and the probe stay
-    auto p = std::make_shared<NdPlan>();
-    p->avoid = avoid;
-    p->barred = barred;
-    nd_build_plan(S.topo, *p, st);
+    auto kept = [&](const thm_system &o) -> std::shared_ptr<NdPlan> {
+        for (const auto &p : o.nd)
+            if (p->avoid == avoid && p->barred == barred && p->matches(S.topo)) return p;
+        return nullptr;
+    };
+    std::shared_ptr<NdPlan> p = kept(S);
+    if (p) return p;
+    for (size_t i = 0; i < others.size() && !p; ++i) p = kept(*others[i]);
+    if (!p) {
+        p = std::make_shared<NdPlan>();
+        p->avoid = avoid;
+        p->barred = barred;
+        nd_build_plan(S.topo, *p, st);
+    }
+    if (S.nd.size() >= ND_KEPT) S.nd.erase(S.nd.begin() + 2);
     S.nd.push_back(p);
     return p;
 }
