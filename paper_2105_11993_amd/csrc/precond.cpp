@@ -598,6 +598,15 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
         if (!s->fac) need.push_back(s);
     if (need.empty()) return;
     const double t0 = now_ms();
+    // a setup that fails half way leaves no factor behind
+    struct Unfinished {
+        std::vector<thm_system *> &sys;
+        bool done = false;
+        ~Unfinished() {
+            if (!done)
+                for (thm_system *s : sys) s->fac.reset();
+        }
+    } unfinished{need};
     // group identical systems
     std::vector<std::shared_ptr<Factor>> facs;
     std::vector<thm_system *> reps;
@@ -901,15 +910,13 @@ void setup_precond(const std::vector<thm_system *> &all, hipStream_t st, bool sh
     int32_t hs = 0;
     THM_HIP(hipMemcpyAsync(&hs, status.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     THM_HIP(hipStreamSynchronize(st));
-    if (hs) {
-        for (thm_system *s : need) s->fac.reset();
-        fail(THM_ESINGULAR, "zero or non-finite pivot while factorising the block preconditioner");
-    }
+    if (hs) fail(THM_ESINGULAR, "zero or non-finite pivot while factorising the block preconditioner");
     const double dt = now_ms() - t0;
     for (auto &f : facs) {
         f->setup_ms = dt;
         f->bytes = 12 * (f->matp_elems + (int64_t)f->kiinv.n + 2 * (int64_t)f->F.n);
     }
+    unfinished.done = true;
 }
 
 }  // namespace thm
