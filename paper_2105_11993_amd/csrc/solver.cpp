@@ -519,13 +519,18 @@ template void Ctx::spmv<float>(int, const int32_t *, const float *, float *, con
 
 // Interface sides with Im s != 0 add to K; a system of 2^28 pairs of cell and member is left to
 // the assembled forms (32-bit pair indices).
-bool Ctx::ensure_cells() {
-    if (cells.desc.n) return true;
+bool Ctx::cells_fit() const {
     for (const SpmvGroup &G : hgroups) {
         const thm_system &S = *sys[G.rep];
         if (S.iface_sides && S.prob.transmission[1] != 0.0) return false;
         if (S.topo.n_cells * G.nm >= (int64_t(1) << 28) || S.n >= (int64_t(1) << 30)) return false;
     }
+    return true;
+}
+
+bool Ctx::ensure_cells() {
+    if (cells.desc.n) return true;
+    if (!cells_fit()) return false;
     CellBatch &C = cells;
     std::vector<CellDesc> h(ngroups);
     std::vector<int64_t> tiles(ngroups), rows(ngroups);
@@ -1610,22 +1615,26 @@ void Ctx::autotune() {
     const thm_system &s0 = *sys[0];
     int nb = 0;
     while ((int64_t(1) << (nb + 1)) <= nrows) ++nb;
+    // Below about 3 million entries (times members) the two launches of the product from the cells lose
+    // to the one of the assembled forms: 64^2 cells of degree 2 in FP64 (2.2 M) 9.2 us against 8.5, 60^2 of
+    // degree 3 (5 M) 12 against 16.  The line lies inside a bucket of sizes, so it is part of the key.
+    const bool from_cells = nnz >= 3000000 && cells_fit();
+    const char *tail = from_cells ? ":cells" : "";
     char key64[128], key32[128];
-    std::snprintf(key64, sizeof key64, "gfx950:d%d:p%d:n%d:b%d:g%d:fp64", s0.topo.dim, s0.topo.p, nb, ns, ngroups);
-    std::snprintf(key32, sizeof key32, "gfx950:d%d:p%d:n%d:b%d:g%d:fp32", s0.topo.dim, s0.topo.p, nb, ns, ngroups);
+    std::snprintf(key64, sizeof key64, "gfx950:d%d:p%d:n%d:b%d:g%d:fp64%s", s0.topo.dim, s0.topo.p, nb, ns, ngroups, tail);
+    std::snprintf(key32, sizeof key32, "gfx950:d%d:p%d:n%d:b%d:g%d:fp32%s", s0.topo.dim, s0.topo.p, nb, ns, ngroups, tail);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         tune_load();
         auto a = g_tune.find(key64), b = g_tune.find(key32);
-        if (a != g_tune.end() && b != g_tune.end()) {
+        auto usable = [&](auto it) { return it != g_tune.end() && (from_cells || it->second != SPMV_CELLS); };
+        if (usable(a) && usable(b)) {
             lpr64 = ready(a->second);
             lpr32 = ready(b->second);
             return;
         }
     }
-    // below about 3 million entries (times members) its two launches lose to the one of the assembled
-    // forms: 64^2 cells of degree 2 in FP64 (2.2 M) 9.2 us against 8.5, 60^2 of degree 3 (5 M) 12 against 16
-    if (nnz >= 3000000 && ensure_cells()) cand.push_back(SPMV_CELLS);
+    if (from_cells) cand.push_back(SPMV_CELLS);
     for (int c : cand) ready(c);
     hipEvent_t e0, e1;
     THM_HIP(hipEventCreate(&e0));

@@ -214,7 +214,8 @@ struct Ctx {
     Sched gsched;
     int ngroups = 0;
     CellBatch cells;         // of the product from the cells (SPMV_CELLS); built on first use
-    bool ensure_cells();     // false: some system's K holds more than its cells' matrices
+    bool cells_fit() const;  // false: some system's K holds more than its cells' matrices
+    bool ensure_cells();     // builds it; false as cells_fit()
     double cell_bytes(double w) const;  // of one product of all systems, w bytes a scalar
     bool spmv_shared = false;  // some group has two or more members
     int64_t xi_total = 0;      // complex entries of the member-interleaved copy (see SpmvGroup::xoff)
