@@ -218,10 +218,9 @@ void launch_nd_invert(const std::vector<NdFront> &h, const NdFront *d, hipStream
         if (f.b <= ND_INV_MAX) n = std::max(n, f.b);
     if (!n) return;
     const size_t lds = sizeof(double) * n * (n | 1);
-    static const hipError_t allowed = hipFuncSetAttribute(reinterpret_cast<const void *>(k_nd_invert),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                          (int)(sizeof(double) * ND_INV_MAX * (ND_INV_MAX | 1)));
-    (void)allowed;  // a refusal shows at the launch
+    // per device, so before every launch; a refusal shows there
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_nd_invert), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)(sizeof(double) * ND_INV_MAX * (ND_INV_MAX | 1)));
     k_nd_invert<<<(unsigned)h.size(), NDI_T, lds, st>>>(d);
     THM_HIP(hipGetLastError());
 }
