@@ -162,6 +162,15 @@ def copy_bandwidth(torch, reps=10):
     return {"bytes": 2 * 4 * n, "ms": ms, "GBps": 2 * 4 * n / ms / 1e6}
 
 
+# sources that decide the traffic of the tree products: the kernels, the trees and the front sizes
+TRAFFIC_SOURCES = ("kernels_nd.hip", "nd.cpp", "nd.h")
+
+
+def source_digest(name):
+    import hashlib
+    return hashlib.sha256(open(os.path.join(ROOT, "paper_2105_11993_amd", "csrc", name), "rb").read()).hexdigest()
+
+
 def summarize_pmc(fetch_dir, write_dir, out_json):
     """Per-launch HBM traffic of the preconditioner's tree products from two rocprofv3 --pmc runs
     of this script (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch), each scaled by what the
@@ -169,7 +178,6 @@ def summarize_pmc(fetch_dir, write_dir, out_json):
     (the timing loop of thm_time_precond, every member active) are used."""
     import csv
     import glob
-    import hashlib
 
     def load(d, counter):
         rows = []
@@ -193,11 +201,10 @@ def summarize_pmc(fetch_dir, write_dir, out_json):
         tail = bcr[-PRECOND_LAUNCHES:]
         res[name] = {"copy_kib_per_launch": copy_kib, "scale": factor,
                      "bcr_kib_per_launch": sum(tail) / len(tail), "bcr_dispatches": len(tail)}
-    src = os.path.join(ROOT, "paper_2105_11993_amd", "csrc", "kernels_prec.hip")
     traffic = sum(v["bcr_kib_per_launch"] * 1024.0 * v["scale"] for v in res.values())
     rec = {"kernel": "k_nd_mfma<float>", "workload": WORKLOAD, "counters": res,
            "hbm_bytes_per_launch": traffic,
-           "kernels_prec_sha256": hashlib.sha256(open(src, "rb").read()).hexdigest()}
+           "sources": {name: source_digest(name) for name in TRAFFIC_SOURCES}}
     with open(out_json, "w") as f:
         json.dump(rec, f, indent=1)
     print(json.dumps(rec, indent=1))
@@ -233,18 +240,20 @@ def summarize_mfma(path, last=PRECOND_LAUNCHES):
 def measured_traffic(algorithmic_bytes_per_launch):
     """HBM bytes per launch of the preconditioner's products from the committed counter runs
     (FETCH_SIZE + WRITE_SIZE, calibrated on a copy of known size), if they were taken on
-    the kernel source as it is now; otherwise None."""
-    import hashlib
-    path = os.path.join(ROOT, "profiles", "k_bcr_mfma_c2_traffic.json")
-    src = os.path.join(ROOT, "paper_2105_11993_amd", "csrc", "kernels_prec.hip")
-    try:
-        rec = json.load(open(path))
-        digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
-    except (OSError, ValueError):
-        return None
-    if rec.get("kernels_prec_sha256") != digest:
-        return None
-    return rec.get("hbm_bytes_per_launch")
+    the kernel sources as they are now; otherwise None.  A record of the tree products names their
+    sources; one of the layered forms' kernel, in kernels_prec.hip, is no figure for the tree products."""
+    for name in ("k_nd_mfma_c2_traffic.json", "k_bcr_mfma_c2_traffic.json"):
+        try:
+            rec = json.load(open(os.path.join(ROOT, "profiles", name)))
+            kernel = rec.get("kernel", "")
+            sources = rec.get("sources") or {"kernels_prec.hip": rec.get("kernels_prec_sha256")}
+            if kernel and not (kernel.startswith("k_nd_") and set(TRAFFIC_SOURCES) <= set(sources)):
+                continue
+            if all(source_digest(f) == d for f, d in sources.items()):
+                return rec.get("hbm_bytes_per_launch")
+        except (OSError, ValueError):
+            continue
+    return None
 
 
 def _form(st, dt=None):
