@@ -62,7 +62,7 @@ typedef enum { THM_KRYLOV_COMPLEX = 0, THM_KRYLOV_REAL = 1 } thm_krylov;
  * M = I + i C_G P K^{-1} P^T (r x r complex, r = |Gamma|; stored once per distinct system).
  * One application costs two applications of K^{-1} plus an r x r complex product.  Use it
  * with THM_FP64: in FP32 the correction cancels and refinement needs many inner steps.
- * Supported for r <= 4096 per subdomain (THM_EUNSUPPORTED above: the setup inverts the
+ * Supported for r <= 16384 per subdomain (THM_EUNSUPPORTED above: the setup inverts the
  * dense 2r x 2r real form of M). */
 typedef enum { THM_PREC_BLOCK = 0, THM_PREC_FULL = 1 } thm_precond;
 /* How THM_FP32_IR refines (either preconditioner).  THM_IR_CLASSIC: FP64 residuals, each
@@ -310,7 +310,7 @@ thm_status thm_time_spmv_systems(int32_t nsys, thm_system *const *sys, int32_t p
  * times the product alone on the copy's current contents. */
 #define THM_SPMV_SELL_GROUP_IL 29
 /* Product from the cells (code 30): the cells' two reference matrices applied on the matrix cores,
- * 1 / mu and -w^2 eps as factors of x, without the assembled K; systems with the same K form
+ * 1 / mu and -w^2 eps as factors of the two products, without the assembled K; systems with the same K form
  * groups as in code 20.  Not for subdomains whose transmission factor has Im s != 0. */
 #define THM_SPMV_CELLS 30
 

@@ -5,9 +5,9 @@
 // edge is cut by lines of O(w (p + 1)) DoFs, so all boxes of one size keep O(N) words together
 // and the whole factor O(N log N), where cyclic reduction over layers of width O(sqrt N) keeps
 // O(N^1.5).  Measured, against cyclic reduction (2D) and block LU (3D): one allocation-free
-// application on 64^2 cells of degree 2 in FP64 58 instead of 140 us; a GMRES step on 11 x 9 x 10
-// cells of degree 1 177 instead of 565 us; the first solve there, with the factorisation, 110
-// instead of 504 ms.
+// application on 64^2 cells of degree 2 in FP64 68 instead of 140 us (60 when repeated on the same
+// vectors); a GMRES step on 11 x 9 x 10 cells of degree 1 177 instead of 565 us; the first solve there,
+// with the factorisation, 110 instead of 504 ms.
 #include "nd.h"
 
 namespace thm {
