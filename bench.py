@@ -223,12 +223,13 @@ def summarize_mfma(path, last=PRECOND_LAUNCHES):
         key = (int(r["Dispatch_Id"]), r["Kernel_Name"].split("(")[0])
         e = per.setdefault(key, {"t": (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-9})
         e[r["Counter_Name"]] = float(r["Counter_Value"])
+    timed = set(sorted(i for i, k in per if "k_nd_mfma<float" in k)[-last:])  # up and down the trees together
     byk = collections.defaultdict(list)
-    for (_, k), v in sorted(per.items()):
-        byk[k].append(v)
+    for (i, k), v in sorted(per.items()):
+        if "k_nd_mfma<float" not in k or i in timed:
+            byk[k].append(v)
     out = {}
-    for k, lst in byk.items():
-        sel = lst[-last:] if "k_nd_mfma<float" in k else lst
+    for k, sel in byk.items():
         t = sum(x["t"] for x in sel)
         fl = sum(x.get("MfmaFlopsF32", 0.0) + x.get("MfmaFlopsF64", 0.0) for x in sel)
         mu = sum(x.get("MfmaUtil", 0.0) * x["t"] for x in sel) / max(t, 1e-300)
