@@ -328,7 +328,7 @@ void gmres_run(Krylov &K, const KOps<T> &ops, const T *b, T *x, const int32_t *m
         launch_solve_reset(B, mask_in, K.running.p, K.iters.p, st);
     }
     if (!graph) {
-        // host-driven: one launch sequence per Arnoldi step; the finish kernel of step j writes
+        // host-driven: one launch sequence per Arnoldi step; the closing kernel of step j writes
         // the systems' flags to host slot j mod NEV, and the host checks the flags of step
         // j - LAG while later steps run
         for (;;) {
@@ -351,7 +351,7 @@ void gmres_run(Krylov &K, const KOps<T> &ops, const T *b, T *x, const int32_t *m
         return;
     }
     // graph replay: a cycle is ceil(m / spc) chunk graphs (steps past a system's end of cycle
-    // find it inactive and do nothing) and one close-and-reopen graph.  The finish kernels of
+    // find it inactive and do nothing) and one close-and-reopen graph.  The closing kernels of
     // chunk c leave the systems' flags in host slot c mod NEV; the host checks chunk c - 1
     // while chunk c runs, and the running flags once per cycle.
     if constexpr (std::is_same_v<T, double>) {

@@ -108,7 +108,7 @@ struct Krylov {
     Batch B;
     int m = 50;
     DBuf<double> H, cs, sn, g, y, hcol, hcol2, hnext, bnorm, beta, resid, est, part, npart;
-    DBuf<double> rtol_d;  // Arnoldi stopping tolerance, read by the (captured) finish kernel
+    DBuf<double> rtol_d;  // Arnoldi stopping tolerance, read by the (captured) closing kernel
     double rtol_h = 0.0;  // host copy (source of the async upload; lives with the workspace)
     DBuf<int32_t> running, active, jcnt, iters;
     DBuf<int32_t> jcol, actc;   // column and flag of the step at hand (see k_arnoldi_close)
